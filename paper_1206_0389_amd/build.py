@@ -16,7 +16,11 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "liblbm.so")
-SOURCES = [os.path.join(HERE, "csrc", "lbm_api.hip"), os.path.join(HERE, "csrc", "lbm_refine.hip")]
+# (source, extra flags): the storage types' launches are compiled side by side
+SOURCES = [(os.path.join(HERE, "csrc", "lbm_api.hip"), []),
+           (os.path.join(HERE, "csrc", "lbm_refine.hip"), [])]
+SOURCES += [(os.path.join(HERE, "csrc", "ops.hip"), ["-DLBM_STORAGE=" + s])
+            for s in ("double", "float", "_Float16")]
 HEADERS = [os.path.join(HERE, "csrc", n) for n in os.listdir(os.path.join(HERE, "csrc"))
            if n.endswith(".h")] + [os.path.join(ROOT, "include", "lbm.h")]
 
@@ -45,9 +49,9 @@ def build(verbose: bool = False) -> str:
     tmp = LIB + ".tmp"
     with tempfile.TemporaryDirectory(prefix="lbm_build_") as tdir:
         objs, procs = [], []
-        for src in SOURCES:
-            obj = os.path.join(tdir, os.path.basename(src) + ".o")
-            cmd = [hipcc()] + flags() + ["-c", "-o", obj, src]
+        for k, (src, extra) in enumerate(SOURCES):
+            obj = os.path.join(tdir, "%d_%s.o" % (k, os.path.basename(src)))
+            cmd = [hipcc()] + flags() + extra + ["-c", "-o", obj, src]
             if verbose:
                 print(" ".join(cmd), flush=True)
             procs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.PIPE,

@@ -4,9 +4,9 @@
 //
 // Storage: one array per population, f[q][z][y][x] (x fastest), deviations
 // f_i - w_i in S = double, float or _Float16; arithmetic in double for
-// double storage and float otherwise. One thread per node, x-rows mapped
-// to consecutive lanes so every population access is a coalesced row
-// segment.
+// double storage and float otherwise. One thread per node, consecutive nodes
+// in memory order on consecutive lanes, so every population access is one
+// contiguous segment (of the row and the next where rows are shorter).
 //
 // AA pattern (two step kinds, one array):
 //   even step: node x reads slot i of its own node (= f_i(x, t)), collides
@@ -86,17 +86,41 @@ struct LatArgs {
   BcArgs bc;
 };
 
-// Which rows (fixed y, z; all x) a launch covers. BOX: y in [y0, y0+ny_in),
-// z in [z0, z0+nz_in) with blockIdx.z = z - z0. LIST: the rows lying on a
-// non-periodic y or z face, enumerated as the zb planes first, then the yb
-// rows of every other z; blockIdx.y is the row number.
+// Division of n < 2^31 by a fixed d: q = (n m) >> (32 + s), m = ceil(2^(31 +
+// b) / d), b = ceil(log2 d): exact, as m d - 2^(31 + b) < d <= 2^b.
+struct FastDiv {
+  uint32_t m, s;  // m = 0: d = 1
+  void set(uint32_t d) {
+    uint32_t b = 0;
+    while (((uint64_t)1 << b) < d) ++b;
+    m = d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << (31 + b)) + d - 1) / d);
+    s = d <= 1 ? 0u : b - 1;
+  }
+  __device__ __forceinline__ uint32_t operator()(uint32_t n) const {
+    return m ? __umulhi(n, m) >> s : n;
+  }
+};
+
+// Which rows (fixed y, z; all x) a launch covers. FLAT: the nodes n0 .. n1 - 1
+// in memory order less those off y in [y0, y0+ny_in), 256 consecutive ones per
+// workgroup whatever the row length. LIST: the rows lying on a non-periodic y
+// or z face, enumerated as the zb planes first, then the yb rows of every
+// other z; blockIdx.y is the row number. BOX (adjoint): y as for FLAT, z in
+// [z0, z0+nz_in) with blockIdx.z = z - z0, a row per workgroup or several.
+//
+// FLAT against BOX for the steps (131 x 97 x 211 MRT FP32, even / odd with
+// walls): 68.9 / 72.5 us against 78.7 / 81.0, as no lane idles at row ends and
+// waves are 256 B runs; 256-node rows: the same. by_xcd: see xcd_tile.
 struct Rows {
   int y0, ny_in, z0, nz_in;
   int zb_n, zb[2];
   int yb_n, yb[2];
   int zi0;
+  uint32_t n0, n1;
+  bool by_xcd;
+  FastDiv by_nx, by_ny;
 };
-enum { ROWS_BOX = 0, ROWS_LIST = 1 };
+enum { ROWS_BOX = 0, ROWS_LIST = 1, ROWS_FLAT = 2 };
 // Boundary handling of a step kernel: none (all faces periodic), general
 // (any face type, any node), or walls only (rows off every non-periodic z
 // face and off y faces that are not walls; x and y faces WALL or periodic).
@@ -113,10 +137,13 @@ struct Compute<double> {
 };
 
 // NT: non-temporal (streaming) hint. The step kernels touch every population
-// once per step, so nothing they load or store is reused from cache except
-// the partial lines at the ends of one-element x shifts; the hint is applied
-// where accesses are aligned to the row (measured: +8 % on the even step,
-// +3 % on the odd step's x-aligned directions, nothing on shifted ones).
+// once per step. In a lattice larger than the last-level cache nothing they
+// load or store is reused from cache except the partial lines at the ends of
+// runs; there the hint is applied where accesses are aligned to memory lines
+// (measured: +8 % on the even step, +3 % on the odd step's x-aligned
+// directions, nothing on shifted ones). It costs where they are not (a line
+// two waves share is fetched and written twice) and where the lattice stays in
+// the cache: see nt_even and nt_odd of the lattice.
 template <typename R, bool NT = false, typename S>
 __device__ __forceinline__ R ld(const S* p) {
   if constexpr (NT)
@@ -446,13 +473,13 @@ __device__ __forceinline__ real pull_term(const BcArgs& b, uint32_t atface, cons
 // bounce-back rule (own slot opp(I), minus the term) and the outflow rule
 // (dropped; a node on the outflow plane also writes the inward population
 // I of its in-plane neighbour, the ghost copy of the next pull).
-template <int Q, int I, typename real, typename S, bool BC, bool EXT = true>
+template <int Q, int I, typename real, typename S, bool BC, bool EXT, bool NT>
 __device__ __forceinline__ void push(const LatArgs& a, S* F, const Node& n, real v,
                                      const real* uin, uint32_t sb, const real* unode) {
   constexpr int IO = opposite<Q>(I);
   const size_t N = (size_t)a.N;
   if constexpr (!BC) {
-    sto<cx(I) == 0>(F + (size_t)I * N, (uint32_t)n.at(cx(I), cy(I), cz(I)) * (uint32_t)sizeof(S),
+    sto<NT && cx(I) == 0>(F + (size_t)I * N, (uint32_t)n.at(cx(I), cy(I), cz(I)) * (uint32_t)sizeof(S),
                     v);
   } else {
     S* normal = F + (size_t)I * N + n.at(cx(I), cy(I), cz(I));
@@ -577,9 +604,26 @@ __device__ __forceinline__ bool node_coords(const LatArgs& a, int& x, int& y, in
   return x < a.nx && y < a.ny;
 }
 
+// The workgroups go round the eight XCDs in launch order; this numbering
+// gives each XCD a contiguous range of 1-D tiles, so that the memory lines two
+// neighbouring tiles share (rows that don't end on one) meet in one L2.
+__device__ __forceinline__ uint32_t xcd_tile(bool by_xcd) {
+  if (!by_xcd) return blockIdx.x;
+  const uint32_t n = gridDim.x, q = n >> 3, r = n & 7u, k = blockIdx.x & 7u;
+  return k * q + min(k, r) + (blockIdx.x >> 3);
+}
+
 template <int ROWS>
 __device__ __forceinline__ bool row_coords(const LatArgs& a, const Rows& r, int& x, int& y,
                                            int& z) {
+  if constexpr (ROWS == ROWS_FLAT) {
+    const uint32_t i = r.n0 + xcd_tile(r.by_xcd) * 256u + threadIdx.x;
+    const uint32_t row = r.by_nx(i), pl = r.by_ny(row);
+    x = (int)(i - row * (uint32_t)a.nx);
+    y = (int)(row - pl * (uint32_t)a.ny);
+    z = (int)pl;
+    return i < r.n1 && y >= r.y0 && y < r.y0 + r.ny_in;
+  }
   x = blockIdx.x * blockDim.x + threadIdx.x;
   if constexpr (ROWS == ROWS_BOX) {
     y = r.y0 + (int)(blockIdx.y * blockDim.y + threadIdx.y);
@@ -604,17 +648,33 @@ __device__ __forceinline__ bool row_coords(const LatArgs& a, const Rows& r, int&
 // written to rec ([Q][N] in the compute type). The record is a runtime
 // switch, so recording and plain steps run the same code and round alike.
 // EXT: interior solids (wall rows and general kernel) or FREESLIP faces
-// (general kernel) present.
-template <int KIND, typename S, bool ODD, int BCM, int ROWS, bool EXT = false>
+// (general kernel) present. NT: streaming hint on the aligned accesses.
+template <int KIND, typename S, bool ODD, int BCM, int ROWS, bool EXT, bool NT>
 __global__ __launch_bounds__(256) void step_kernel(const LatArgs a, const Rows r, long long t,
                                                    typename Compute<S>::type* rec) {
   using M = Model<KIND>;
   using real = typename Compute<S>::type;
   constexpr int Q = M::Q;
   constexpr bool BC = BCM == BC_GENERAL;
-  int x, y, z;
-  if (!row_coords<ROWS>(a, r, x, y, z)) return;
-  const Node n = make_node(a, x, y, z);
+  Node n;
+  if constexpr (ROWS == ROWS_FLAT && !ODD && !EXT) {
+    // even steps touch the node's own slots and, on the outflow plane, the
+    // ghost plane: no coordinates, the place in the plane alone
+    const uint32_t i = r.n0 + xcd_tile(r.by_xcd) * 256u + threadIdx.x;
+    if (i >= r.n1) return;
+    n.self = (int)i;
+    n.atface = 0;
+    n.xo[1] = n.yo[1] = 0;
+    if constexpr (BC) {
+      const uint32_t plane = (uint32_t)a.nx * (uint32_t)a.ny, top = (uint32_t)a.N - plane;
+      n.atface = ((i < plane ? 16u : 0u) | (i >= top ? 32u : 0u)) & a.bc.nonper;
+      n.xo[1] = (int)(i >= top ? i - top : i);
+    }
+  } else {
+    int x, y, z;
+    if (!row_coords<ROWS>(a, r, x, y, z)) return;
+    n = make_node(a, x, y, z);
+  }
   S* __restrict__ F = (S*)a.f;
   const size_t N = (size_t)a.N;
   // interior solids: solid nodes are skipped (the even step runs this only
@@ -642,24 +702,24 @@ __global__ __launch_bounds__(256) void step_kernel(const LatArgs a, const Rows r
   if constexpr (!ODD) {
     static_for<0, Q>([&](auto ic) {
       constexpr int I = decltype(ic)::value;
-      f[I] = ldo<real, true>(F + (size_t)I * N, self_off);
+      f[I] = ldo<real, NT>(F + (size_t)I * N, self_off);
     });
   } else {
     if constexpr (BCM == BC_WALLS) {
       static_for<0, Q>([&](auto ic) {
         constexpr int I = decltype(ic)::value;
-        f[I] = pull_walls<Q, I, real, cx(I) == 0, EXT>(a, F, n, sb);
+        f[I] = pull_walls<Q, I, real, NT && cx(I) == 0, EXT>(a, F, n, sb);
       });
     } else if constexpr (BCM == BC_NONE) {
       static_for<0, Q>([&](auto ic) {
         constexpr int I = decltype(ic)::value;
-        f[I] = ldo<real, cx(I) == 0>(F + (size_t)opposite<Q>(I) * N,
+        f[I] = ldo<real, NT && cx(I) == 0>(F + (size_t)opposite<Q>(I) * N,
                                      (uint32_t)n.at(-cx(I), -cy(I), -cz(I)) * (uint32_t)sizeof(S));
       });
     } else {
       static_for<0, Q>([&](auto ic) {
         constexpr int I = decltype(ic)::value;
-        f[I] = ld<real, !BC && cx(I) == 0>(pull_addr<Q, I, S, BC, EXT>(a, F, n, sb));
+        f[I] = ld<real>(pull_addr<Q, I, S, BC, EXT>(a, F, n, sb));
       });
       if constexpr (BC) {
         const real up[3] = {real(uin_prev[0]), real(uin_prev[1]), real(uin_prev[2])};
@@ -709,7 +769,7 @@ __global__ __launch_bounds__(256) void step_kernel(const LatArgs a, const Rows r
           v = -v + pressure_pair<KQ, I, real>(
                        real(pressure_drho(a.bc, crossed & a.bc.pressure)), unode);
       }
-      sto<true>(F + (size_t)opposite<Q>(I) * N, self_off, v);
+      sto<NT>(F + (size_t)opposite<Q>(I) * N, self_off, v);
     });
     if constexpr (BC) {
       if (n.atface & a.bc.outflow) {
@@ -726,65 +786,72 @@ __global__ __launch_bounds__(256) void step_kernel(const LatArgs a, const Rows r
     if constexpr (BCM == BC_WALLS) {
       static_for<0, Q>([&](auto ic) {
         constexpr int I = decltype(ic)::value;
-        push_walls<Q, I, real, cx(I) == 0, EXT>(a, F, n, f[I], sb);
+        push_walls<Q, I, real, NT && cx(I) == 0, EXT>(a, F, n, f[I], sb);
       });
     } else {
       const real un[3] = {real(uin_now[0]), real(uin_now[1]), real(uin_now[2])};
       static_for<0, Q>([&](auto ic) {
         constexpr int I = decltype(ic)::value;
-        push<Q, I, real, S, BC, EXT>(a, F, n, f[I], un, sb, unode);
+        push<Q, I, real, S, BC, EXT, NT>(a, F, n, f[I], un, sb, unode);
       });
     }
   }
 }
 
-// Even step of FP16 storage with two x-neighbouring nodes per lane (x even):
-// one 4-byte load and store per population serve both, where one node per
-// lane moves 2 bytes per access. Each node collides in FP32 exactly as in
-// step_kernel (bitwise the same result). No solids, links, pressure faces or
-// recording (those lattices take step_kernel).
+// Even step of FP16 storage with two neighbouring nodes per lane (an even
+// number of nodes): one 4-byte load and store per population serve both,
+// where one node per lane moves 2 bytes per access. Each node collides in
+// FP32 exactly as in step_kernel (bitwise the same result). No solids, links,
+// pressure faces or recording (those lattices take step_kernel).
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-template <int KIND, bool BC>
-__global__ __launch_bounds__(256) void step_even_pair_kernel(const LatArgs a) {
+template <int KIND, bool BC, bool NT>
+__global__ __launch_bounds__(256) void step_even_pair_kernel(const LatArgs a, bool by_xcd) {
   using M = Model<KIND>;
   constexpr int Q = M::Q;
-  const int x = 2 * (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  const int y = (int)(blockIdx.y * blockDim.y + threadIdx.y);
-  const int z = (int)blockIdx.z;
-  if (x >= a.nx || y >= a.ny) return;
+  const uint32_t i = 2u * (xcd_tile(by_xcd) * 256u + threadIdx.x);
+  if (i >= (uint32_t)a.N) return;
   _Float16* __restrict__ F = (_Float16*)a.f;
   const size_t N = (size_t)a.N;
-  const uint32_t off = (uint32_t)((((size_t)z * a.ny + y) * a.nx + x) * sizeof(_Float16));
+  const uint32_t off = i * (uint32_t)sizeof(_Float16);
   half2_t v[Q];
   static_for<0, Q>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
-    v[I] = __builtin_nontemporal_load((const half2_t*)((const char*)(F + (size_t)I * N) + off));
+    const half2_t* p = (const half2_t*)((const char*)(F + (size_t)I * N) + off);
+    if constexpr (NT)
+      v[I] = __builtin_nontemporal_load(p);
+    else
+      v[I] = *p;
   });
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     float f[Q];
 #pragma unroll
-    for (int i = 0; i < Q; ++i) f[i] = float(v[i][k]);
+    for (int q = 0; q < Q; ++q) f[q] = float(v[q][k]);
     M::collide(f, a);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) v[i][k] = _Float16(f[i]);
+    for (int q = 0; q < Q; ++q) v[q][k] = _Float16(f[q]);
     if constexpr (BC) {
-      const Node n = make_node(a, x + k, y, z);
-      if (n.atface & a.bc.outflow) {
+      // the outflow plane's ghost copies (the outflow face is a z face)
+      const uint32_t plane = (uint32_t)a.nx * (uint32_t)a.ny, top = (uint32_t)a.N - plane;
+      const uint32_t node = i + (uint32_t)k;
+      const uint32_t at = ((node < plane ? 16u : 0u) | (node >= top ? 32u : 0u)) & a.bc.outflow;
+      if (at) {
         _Float16* G = (_Float16*)a.ghost;
-        const long long g = n.yo[1] + n.xo[1];
+        const uint32_t g = node >= top ? node - top : node;
         static_for<0, Q>([&](auto ic) {
           constexpr int I = decltype(ic)::value;
-          if (n.atface & a.bc.outflow & pull_faces(I))
-            st(G + (size_t)I * (size_t)a.bc.ghost_n + g, f[I]);
+          if (at & pull_faces(I)) st(G + (size_t)I * (size_t)a.bc.ghost_n + g, f[I]);
         });
       }
     }
   }
   static_for<0, Q>([&](auto ic) {
     constexpr int I = decltype(ic)::value;
-    __builtin_nontemporal_store(v[I],
-                                (half2_t*)((char*)(F + (size_t)opposite<Q>(I) * N) + off));
+    half2_t* p = (half2_t*)((char*)(F + (size_t)opposite<Q>(I) * N) + off);
+    if constexpr (NT)
+      __builtin_nontemporal_store(v[I], p);
+    else
+      *p = v[I];
   });
 }
 

@@ -1,6 +1,6 @@
 // Host runtime of the C ABI declared in include/lbm.h: validation, memory
-// layout inside the caller's block, launch configuration and dispatch over
-// model x storage x step parity x boundary handling.
+// layout inside the caller's block and launch configuration. The launches
+// that depend on the storage type are in ops.hip.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -15,45 +15,10 @@
 #include "adjoint.h"
 #include "jetprofile.h"
 #include "kernels.h"
+#include "lattice.h"
 #include "trace.h"
 
 using namespace lbm;
-
-struct lbm_lattice {
-  lbm_config cfg;
-  int kind;  // 0 MRT Table 1, 1 MRT d'Humieres, 2 FCLB
-  int Q;
-  size_t N;
-  size_t elem;  // bytes per stored value
-  hipStream_t stream;
-  // bound memory
-  char* base = nullptr;
-  size_t bytes = 0;
-  size_t off_ghost = 0, off_partial = 0, off_result = 0, req = 0;
-  size_t ghost_n_max = 0;
-  size_t nblocks = 0;
-  // state
-  int64_t t = 0;
-  int parity = 0;
-  bool has_bc = false;
-  bool solids = false;  // interior solid nodes set (general kernel only)
-  // interpolated bounce-back links (caller-owned device buffers)
-  const int32_t* link_nodes = nullptr;
-  const float* link_q = nullptr;
-  long long nlinks = 0;
-  LatArgs args;
-  dim3 grid, block;
-  // odd steps with boundaries split into wall rows (x and y faces walls or
-  // periodic, see pull_walls) and the rows on the other non-periodic faces
-  bool split_odd = false;
-  Rows rows_all, rows_inner, rows_bnd;
-  dim3 grid_inner, grid_bnd, block_bnd;
-  // health check inside lbm_step (lbm_set_check)
-  int64_t check_every = 0;
-  double check_tol = -1.0, check_m0 = 0.0;
-  // per-launch timing (LBM_TRACE=1 at creation)
-  std::unique_ptr<Tracer> tracer = std::make_unique<Tracer>();
-};
 
 namespace {
 
@@ -77,144 +42,6 @@ void launch_shape(lbm_lattice* L) {
   L->nblocks = (size_t)L->grid.x * L->grid.y * L->grid.z;
 }
 
-template <int KIND, typename S, bool ODD, int BCM, int ROWS, bool EXT = false>
-void launch_step(const lbm_lattice* L, dim3 grid, dim3 block, const Rows& r, long long t,
-                 void* rec) {
-  TraceScope ts(L->tracer.get(), L->stream, LBM_TRACE_LABEL("step_kernel"));
-  hipLaunchKernelGGL((step_kernel<KIND, S, ODD, BCM, ROWS, EXT>), grid, block, 0, L->stream,
-                     L->args, r, t, (typename Compute<S>::type*)rec);
-}
-
-template <int KIND, typename S, bool EXT>
-void step_model_ext(const lbm_lattice* L, bool odd, long long t, void* rec) {
-  if (!L->has_bc) {
-    if (odd)
-      launch_step<KIND, S, true, BC_NONE, ROWS_BOX>(L, L->grid, L->block, L->rows_all, t, rec);
-    else
-      launch_step<KIND, S, false, BC_NONE, ROWS_BOX>(L, L->grid, L->block, L->rows_all, t, rec);
-  } else if (!odd) {
-    launch_step<KIND, S, false, BC_GENERAL, ROWS_BOX, EXT>(L, L->grid, L->block, L->rows_all, t,
-                                                           rec);
-  } else if (!L->split_odd) {
-    launch_step<KIND, S, true, BC_GENERAL, ROWS_BOX, EXT>(L, L->grid, L->block, L->rows_all, t,
-                                                          rec);
-  } else {
-    // wall rows: the solid variant only with solids (free slip never
-    // reaches them)
-    if (L->grid_inner.y > 0 && L->grid_inner.z > 0) {
-      if (L->solids)
-        launch_step<KIND, S, true, BC_WALLS, ROWS_BOX, true>(L, L->grid_inner, L->block,
-                                                             L->rows_inner, t, rec);
-      else
-        launch_step<KIND, S, true, BC_WALLS, ROWS_BOX>(L, L->grid_inner, L->block,
-                                                       L->rows_inner, t, rec);
-    }
-    if (L->grid_bnd.y > 0)
-      launch_step<KIND, S, true, BC_GENERAL, ROWS_LIST, EXT>(L, L->grid_bnd, L->block_bnd,
-                                                             L->rows_bnd, t, rec);
-  }
-}
-
-// Lattices without interior solids, FREESLIP or PRESSURE faces run the
-// general kernel compiled without their rules. The even step touches only
-// each node's own slots, which no other node reads: solid nodes may run it
-// (their populations are never read) and free slip has no even-step rule,
-// so there the rules are compiled in only for PRESSURE faces.
-template <int KIND, typename S>
-void step_model(const lbm_lattice* L, bool odd, long long t, void* rec) {
-  const bool ext = odd ? (L->solids || L->args.bc.freeslip || L->args.bc.pressure)
-                       : L->args.bc.pressure != 0;
-  if constexpr (std::is_same_v<S, _Float16>) {
-    // FP16 even steps: two nodes per lane (the pair kernel's rows)
-    if (!odd && !ext && rec == nullptr && L->cfg.nx % 2 == 0) {
-      const int hx = L->cfg.nx / 2;
-      const int bx = hx < 256 ? hx : 256;
-      int by = 256 / bx;
-      if (by > L->cfg.ny) by = L->cfg.ny;
-      const dim3 block(bx, by, 1);
-      const dim3 grid((hx + bx - 1) / bx, (L->cfg.ny + by - 1) / by, L->cfg.nz);
-      TraceScope ts(L->tracer.get(), L->stream,
-                    L->has_bc ? "step_even_pair_kernel (FP16, boundaries)"
-                              : "step_even_pair_kernel (FP16)");
-      if (L->has_bc)
-        hipLaunchKernelGGL((step_even_pair_kernel<KIND, true>), grid, block, 0, L->stream,
-                           L->args);
-      else
-        hipLaunchKernelGGL((step_even_pair_kernel<KIND, false>), grid, block, 0, L->stream,
-                           L->args);
-      return;
-    }
-  }
-  if (ext)
-    step_model_ext<KIND, S, true>(L, odd, t, rec);
-  else
-    step_model_ext<KIND, S, false>(L, odd, t, rec);
-}
-
-template <typename S>
-void step_dispatch_s(lbm_lattice* L, bool odd, long long t) {
-  switch (L->kind) {
-    case 0: step_model<0, S>(L, odd, t, nullptr); break;
-    case 1: step_model<1, S>(L, odd, t, nullptr); break;
-    case 3: step_model<3, S>(L, odd, t, nullptr); break;
-    default: step_model<2, S>(L, odd, t, nullptr); break;
-  }
-}
-
-void step_dispatch(lbm_lattice* L, bool odd, long long t) {
-  switch (L->cfg.storage) {
-    case LBM_F64: step_dispatch_s<double>(L, odd, t); break;
-    case LBM_F32: step_dispatch_s<float>(L, odd, t); break;
-    default: step_dispatch_s<_Float16>(L, odd, t); break;
-  }
-}
-
-// Interpolated bounce-back over the link list after a step.
-template <typename S>
-void links_dispatch_s(const lbm_lattice* L, bool after_odd) {
-  const dim3 grid((unsigned)((L->nlinks + 7) / 8)), block(256);  // 32 lanes per node
-  TraceScope ts(L->tracer.get(), L->stream, "link_kernel (interpolated bounce-back)");
-  auto go = [&](auto q_c, auto odd_c) {
-    constexpr int Q = decltype(q_c)::value;
-    constexpr bool ODD = decltype(odd_c)::value;
-    hipLaunchKernelGGL((link_kernel<Q, S, ODD>), grid, block, 0, L->stream, L->args,
-                       L->link_nodes, L->link_q, L->nlinks);
-  };
-  if (L->Q == 27) {
-    if (after_odd) go(std::integral_constant<int, 27>{}, std::true_type{});
-    else go(std::integral_constant<int, 27>{}, std::false_type{});
-  } else {
-    if (after_odd) go(std::integral_constant<int, 19>{}, std::true_type{});
-    else go(std::integral_constant<int, 19>{}, std::false_type{});
-  }
-}
-
-void links_dispatch(const lbm_lattice* L, bool after_odd) {
-  switch (L->cfg.storage) {
-    case LBM_F64: links_dispatch_s<double>(L, after_odd); break;
-    case LBM_F32: links_dispatch_s<float>(L, after_odd); break;
-    default: links_dispatch_s<_Float16>(L, after_odd); break;
-  }
-}
-
-// One FCLB or MRT-LES step that also records the pre-collision state (FP64
-// and FP32 storage: the adjoint's recomputation).
-template <int KIND>
-void step_record_kind(lbm_lattice* L, bool odd, long long t, void* rec) {
-  if (L->cfg.storage == LBM_F64)
-    step_model<KIND, double>(L, odd, t, rec);
-  else
-    step_model<KIND, float>(L, odd, t, rec);
-}
-
-void step_record_dispatch(lbm_lattice* L, bool odd, long long t, void* rec) {
-  switch (L->kind) {
-    case 0: step_record_kind<0>(L, odd, t, rec); break;
-    case 1: step_record_kind<1>(L, odd, t, rec); break;
-    default: step_record_kind<2>(L, odd, t, rec); break;
-  }
-}
-
 // Slabs spanned by a population and its opposite (see max_opposite_distance).
 double slab_span(int Q) {
   return 1.0 + (Q == 27 ? max_opposite_distance<27>() : max_opposite_distance<19>());
@@ -229,6 +56,25 @@ void plan_rows(lbm_lattice* L) {
   all.ny_in = ny;
   all.z0 = 0;
   all.nz_in = nz;
+  all.n0 = 0;
+  all.n1 = (uint32_t)L->N;
+  all.by_nx.set((uint32_t)nx);
+  all.by_ny.set((uint32_t)ny);
+  // Lattices that the last-level cache (256 MB) holds from step to step take
+  // their tiles by XCD and no streaming hint; measured per step (even / odd
+  // with walls), 96x112x224 MRT FP32 (183 MB): 54.0 / 56.5 us against 74.5 /
+  // 67.4 with the hint in launch order. Beyond it the eight far apart ranges
+  // cost more than the shared lines (256x256x512 FCLB FP32, 3.6 GB: 1296 /
+  // 1514 against 1251 / 1396 us) and the hint pays (1251 against 1351 us),
+  // where the accesses are whole lines: odd steps on 190-node rows (1.0 GB)
+  // 440 us with it, 413 without; their even steps, whose slabs are aligned,
+  // 361 and 393.
+  const double bytes = (double)L->N * L->Q * (double)L->elem;
+  const bool resident = bytes <= 256.0 * 1048576.0;
+  all.by_xcd = resident;
+  L->nt_even = !resident && (L->N * L->elem) % 128 == 0;
+  L->nt_odd = !resident && ((size_t)nx * L->elem) % 128 == 0;
+  L->tiles_all = (unsigned)((L->N + 255) / 256);
   L->rows_all = all;
   const bool znp = (np & 48u) != 0;
   // y faces that are walls stay in the wall rows; other non-periodic y
@@ -243,6 +89,10 @@ void plan_rows(lbm_lattice* L) {
     in.z0 = 1;
     in.nz_in = nz - 2;
   }
+  const size_t plane = (size_t)nx * ny;
+  in.n0 = (uint32_t)(in.z0 * plane);
+  in.n1 = in.ny_in > 0 && in.nz_in > 0 ? in.n0 + (uint32_t)(in.nz_in * plane) : in.n0;
+  L->tiles_inner = (in.n1 - in.n0 + 255) / 256;
   L->rows_inner = in;
   Rows b{};
   if (znp) {
@@ -272,29 +122,13 @@ void plan_rows(lbm_lattice* L) {
   L->grid_bnd = dim3((nx + bbx - 1) / bbx, (unsigned)(nrows > 0 ? nrows : 0), 1);
 }
 
-// Runs fn<KIND, S, BC>() for the lattice's configuration.
+// Runs fn(a value of the lattice's storage type).
 template <typename Fn>
-void with_config(const lbm_lattice* L, Fn&& fn) {
-  auto by_s = [&](auto kind_c) {
-    constexpr int KIND = decltype(kind_c)::value;
-    auto by_bc = [&](auto s_tag) {
-      using S = typename decltype(s_tag)::type;
-      if (L->has_bc)
-        fn(std::integral_constant<int, KIND>{}, s_tag, std::true_type{});
-      else
-        fn(std::integral_constant<int, KIND>{}, s_tag, std::false_type{});
-    };
-    switch (L->cfg.storage) {
-      case LBM_F64: by_bc(std::type_identity<double>{}); break;
-      case LBM_F32: by_bc(std::type_identity<float>{}); break;
-      default: by_bc(std::type_identity<_Float16>{}); break;
-    }
-  };
-  switch (L->kind) {
-    case 0: by_s(std::integral_constant<int, 0>{}); break;
-    case 1: by_s(std::integral_constant<int, 1>{}); break;
-    case 3: by_s(std::integral_constant<int, 3>{}); break;
-    default: by_s(std::integral_constant<int, 2>{}); break;
+void by_storage(const lbm_lattice* L, Fn&& fn) {
+  switch (L->cfg.storage) {
+    case LBM_F64: fn(double()); break;
+    case LBM_F32: fn(float()); break;
+    default: fn(_Float16()); break;
   }
 }
 
@@ -317,13 +151,7 @@ int reduce_now(lbm_lattice* L, double out[5]) {
   double* result = (double*)(L->base + L->off_result);
   {
     TraceScope ts(L->tracer.get(), L->stream, "reduce_partial_kernel + reduce_final_kernel");
-    with_config(L, [&](auto kind_c, auto s_tag, auto bc_c) {
-      constexpr int KIND = decltype(kind_c)::value;
-      using S = typename decltype(s_tag)::type;
-      constexpr bool BC = decltype(bc_c)::value;
-      hipLaunchKernelGGL((reduce_partial_kernel<KIND, S, BC>), L->grid, L->block, 0, L->stream,
-                         L->args, L->parity, (long long)L->t, partial);
-    });
+    by_storage(L, [&](auto s) { Ops<decltype(s)>::reduce_partial(L, L->grid, partial); });
     hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(256), 0, L->stream, partial,
                        L->nblocks, result);
   }
@@ -575,15 +403,8 @@ int lbm_init_equilibrium(lbm_lattice* L, const void* drho, const void* u, int dt
                          int64_t t0) {
   if (!L || !drho || !u || !valid_dtype(dtype)) return LBM_EINVAL;
   if (!L->base) return LBM_EUNBOUND;
-  with_config(L, [&](auto kind_c, auto s_tag, auto) {
-    constexpr int KIND = decltype(kind_c)::value;
-    using S = typename decltype(s_tag)::type;
-    if (dtype == LBM_DTYPE_F64)
-      hipLaunchKernelGGL((init_equilibrium_kernel<KIND, S, double>), L->grid, L->block, 0,
-                         L->stream, L->args, (const double*)drho, (const double*)u);
-    else
-      hipLaunchKernelGGL((init_equilibrium_kernel<KIND, S, float>), L->grid, L->block, 0,
-                         L->stream, L->args, (const float*)drho, (const float*)u);
+  by_storage(L, [&](auto s) {
+    Ops<decltype(s)>::init_equilibrium(L, drho, u, dtype == LBM_DTYPE_F64);
   });
   const int rc = check_launch();
   if (rc) return rc;
@@ -595,16 +416,7 @@ int lbm_init_equilibrium(lbm_lattice* L, const void* drho, const void* u, int dt
 int lbm_set_populations(lbm_lattice* L, const void* f, int dtype, int64_t t0) {
   if (!L || !f || !valid_dtype(dtype)) return LBM_EINVAL;
   if (!L->base) return LBM_EUNBOUND;
-  with_config(L, [&](auto kind_c, auto s_tag, auto) {
-    constexpr int Q = Model<decltype(kind_c)::value>::Q;
-    using S = typename decltype(s_tag)::type;
-    if (dtype == LBM_DTYPE_F64)
-      hipLaunchKernelGGL((set_populations_kernel<Q, S, double>), L->grid, L->block, 0,
-                         L->stream, L->args, (const double*)f);
-    else
-      hipLaunchKernelGGL((set_populations_kernel<Q, S, float>), L->grid, L->block, 0,
-                         L->stream, L->args, (const float*)f);
-  });
+  by_storage(L, [&](auto s) { Ops<decltype(s)>::set_populations(L, f, dtype == LBM_DTYPE_F64); });
   const int rc = check_launch();
   if (rc) return rc;
   L->t = t0;
@@ -615,17 +427,7 @@ int lbm_set_populations(lbm_lattice* L, const void* f, int dtype, int64_t t0) {
 int lbm_get_populations(lbm_lattice* L, void* f, int dtype) {
   if (!L || !f || !valid_dtype(dtype)) return LBM_EINVAL;
   if (!L->base) return LBM_EUNBOUND;
-  with_config(L, [&](auto kind_c, auto s_tag, auto bc_c) {
-    constexpr int Q = Model<decltype(kind_c)::value>::Q;
-    using S = typename decltype(s_tag)::type;
-    constexpr bool BC = decltype(bc_c)::value;
-    if (dtype == LBM_DTYPE_F64)
-      hipLaunchKernelGGL((get_populations_kernel<Q, S, BC, double>), L->grid, L->block, 0,
-                         L->stream, L->args, L->parity, (long long)L->t, (double*)f);
-    else
-      hipLaunchKernelGGL((get_populations_kernel<Q, S, BC, float>), L->grid, L->block, 0,
-                         L->stream, L->args, L->parity, (long long)L->t, (float*)f);
-  });
+  by_storage(L, [&](auto s) { Ops<decltype(s)>::get_populations(L, f, dtype == LBM_DTYPE_F64); });
   return check_launch();
 }
 
@@ -633,8 +435,11 @@ int lbm_step(lbm_lattice* L, int64_t n) {
   if (!L || n < 0) return LBM_EINVAL;
   if (!L->base) return LBM_EUNBOUND;
   for (int64_t k = 0; k < n; ++k) {
-    step_dispatch(L, L->parity == 1, (long long)L->t);
-    if (L->nlinks > 0) links_dispatch(L, L->parity == 1);
+    by_storage(L, [&](auto s) {
+      Ops<decltype(s)>::step(L, L->parity == 1, (long long)L->t, nullptr);
+    });
+    if (L->nlinks > 0)
+      by_storage(L, [&](auto s) { Ops<decltype(s)>::links(L, L->parity == 1); });
     L->t += 1;
     L->parity ^= 1;
     if (L->check_every > 0 && L->t % L->check_every == 0) {
@@ -652,7 +457,9 @@ int lbm_step_record(lbm_lattice* L, void* rec, int dtype) {
       L->args.bc.pressure)
     return LBM_EINVAL;
   if (dtype != (L->cfg.storage == LBM_F64 ? LBM_DTYPE_F64 : LBM_DTYPE_F32)) return LBM_EINVAL;
-  step_record_dispatch(L, L->parity == 1, (long long)L->t, rec);
+  by_storage(L, [&](auto s) {
+    Ops<decltype(s)>::step(L, L->parity == 1, (long long)L->t, rec);
+  });
   L->t += 1;
   L->parity ^= 1;
   return check_launch();
@@ -663,18 +470,8 @@ int lbm_get_macroscopic(lbm_lattice* L, void* rho, void* u, int dtype, int rho_m
   if (rho_mode != LBM_RHO_FULL && rho_mode != LBM_RHO_DEVIATION) return LBM_EINVAL;
   if (!L->base) return LBM_EUNBOUND;
   if (!rho && !u) return LBM_OK;
-  with_config(L, [&](auto kind_c, auto s_tag, auto bc_c) {
-    constexpr int KIND = decltype(kind_c)::value;
-    using S = typename decltype(s_tag)::type;
-    constexpr bool BC = decltype(bc_c)::value;
-    if (dtype == LBM_DTYPE_F64)
-      hipLaunchKernelGGL((macroscopic_kernel<KIND, S, BC, double>), L->grid, L->block, 0,
-                         L->stream, L->args, L->parity, (long long)L->t, (double*)rho,
-                         (double*)u, rho_mode);
-    else
-      hipLaunchKernelGGL((macroscopic_kernel<KIND, S, BC, float>), L->grid, L->block, 0,
-                         L->stream, L->args, L->parity, (long long)L->t, (float*)rho,
-                         (float*)u, rho_mode);
+  by_storage(L, [&](auto s) {
+    Ops<decltype(s)>::macroscopic(L, rho, u, dtype == LBM_DTYPE_F64, rho_mode);
   });
   return check_launch();
 }
@@ -733,13 +530,7 @@ int lbm_set_links(lbm_lattice* L, const int32_t* nodes, const float* q, int64_t 
 int lbm_stats_accumulate(lbm_lattice* L, double* sums) {
   if (!L || !sums) return LBM_EINVAL;
   if (!L->base) return LBM_EUNBOUND;
-  with_config(L, [&](auto kind_c, auto s_tag, auto bc_c) {
-    constexpr int KIND = decltype(kind_c)::value;
-    using S = typename decltype(s_tag)::type;
-    constexpr bool BC = decltype(bc_c)::value;
-    hipLaunchKernelGGL((stats_accumulate_kernel<KIND, S, BC>), L->grid, L->block, 0, L->stream,
-                       L->args, L->parity, (long long)L->t, sums);
-  });
+  by_storage(L, [&](auto s) { Ops<decltype(s)>::stats_accumulate(L, sums); });
   return check_launch();
 }
 
@@ -836,13 +627,7 @@ int lbm_reduce_static(lbm_lattice* L, double* out) {
   size_t gz = kStaticPartials / plane;
   if (gz > (size_t)L->grid.z) gz = L->grid.z;
   const dim3 grid(L->grid.x, L->grid.y, (unsigned)gz);
-  with_config(L, [&](auto kind_c, auto s_tag, auto bc_c) {
-    constexpr int KIND = decltype(kind_c)::value;
-    using S = typename decltype(s_tag)::type;
-    constexpr bool BC = decltype(bc_c)::value;
-    hipLaunchKernelGGL((reduce_partial_kernel<KIND, S, BC>), grid, L->block, 0, L->stream,
-                       L->args, L->parity, (long long)L->t, partial);
-  });
+  by_storage(L, [&](auto s) { Ops<decltype(s)>::reduce_partial(L, grid, partial); });
   rc = check_launch();
   if (rc) return rc;
   hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(256), 0, L->stream, partial,
@@ -903,18 +688,8 @@ int lbm_probe_ke(lbm_lattice* L, const int32_t lo[3], const int32_t hi[3], void*
   double* partial = (double*)(L->base + L->off_partial);
   double* result = (double*)(L->base + L->off_result);
   const int3 l3 = make_int3(lo[0], lo[1], lo[2]), h3 = make_int3(hi[0], hi[1], hi[2]);
-  with_config(L, [&](auto kind_c, auto s_tag, auto bc_c) {
-    constexpr int KIND = decltype(kind_c)::value;
-    using S = typename decltype(s_tag)::type;
-    constexpr bool BC = decltype(bc_c)::value;
-    if (dtype == LBM_DTYPE_F64)
-      hipLaunchKernelGGL((probe_kernel<KIND, S, BC, double>), L->grid, L->block, 0, L->stream,
-                         L->args, L->parity, (long long)L->t, l3, h3, scale, (double*)lambda,
-                         partial);
-    else
-      hipLaunchKernelGGL((probe_kernel<KIND, S, BC, float>), L->grid, L->block, 0, L->stream,
-                         L->args, L->parity, (long long)L->t, l3, h3, scale, (float*)lambda,
-                         partial);
+  by_storage(L, [&](auto s) {
+    Ops<decltype(s)>::probe(L, l3, h3, scale, lambda, dtype == LBM_DTYPE_F64, partial);
   });
   int rc = check_launch();
   if (rc) return rc;

@@ -1,0 +1,254 @@
+// Launches of the kernels that depend on the storage type of a lattice, over
+// model x step parity x boundary handling. Compiled once per type, with
+// LBM_STORAGE set to it.
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <string>
+#include <type_traits>
+
+#include "adjoint.h"
+#include "lattice.h"
+
+using namespace lbm;
+
+namespace {
+
+template <int KIND, typename S, bool ODD, int BCM, int ROWS, bool EXT, bool NT>
+void launch_step(const lbm_lattice* L, dim3 grid, dim3 block, const Rows& r, long long t,
+                 void* rec) {
+  TraceScope ts(L->tracer.get(), L->stream, LBM_TRACE_LABEL("step_kernel"));
+  hipLaunchKernelGGL((step_kernel<KIND, S, ODD, BCM, ROWS, EXT, NT>), grid, block, 0, L->stream,
+                     L->args, r, t, (typename Compute<S>::type*)rec);
+}
+
+template <int KIND, typename S, bool EXT, bool NT>
+void step_model_ext(const lbm_lattice* L, bool odd, long long t, void* rec) {
+  const dim3 block(256), grid(L->tiles_all);
+  if (!L->has_bc) {
+    if (odd)
+      launch_step<KIND, S, true, BC_NONE, ROWS_FLAT, false, NT>(L, grid, block, L->rows_all, t,
+                                                                rec);
+    else
+      launch_step<KIND, S, false, BC_NONE, ROWS_FLAT, false, NT>(L, grid, block, L->rows_all, t,
+                                                                 rec);
+  } else if (!odd) {
+    launch_step<KIND, S, false, BC_GENERAL, ROWS_FLAT, EXT, NT>(L, grid, block, L->rows_all, t,
+                                                                rec);
+  } else if (!L->split_odd) {
+    launch_step<KIND, S, true, BC_GENERAL, ROWS_FLAT, EXT, false>(L, grid, block, L->rows_all, t,
+                                                                  rec);
+  } else {
+    // wall rows: the solid variant only with solids (free slip never
+    // reaches them)
+    if (L->tiles_inner > 0) {
+      const dim3 inner(L->tiles_inner);
+      if (L->solids)
+        launch_step<KIND, S, true, BC_WALLS, ROWS_FLAT, true, NT>(L, inner, block, L->rows_inner,
+                                                                  t, rec);
+      else
+        launch_step<KIND, S, true, BC_WALLS, ROWS_FLAT, false, NT>(L, inner, block, L->rows_inner,
+                                                                   t, rec);
+    }
+    if (L->grid_bnd.y > 0)
+      launch_step<KIND, S, true, BC_GENERAL, ROWS_LIST, EXT, false>(L, L->grid_bnd, L->block_bnd,
+                                                                    L->rows_bnd, t, rec);
+  }
+}
+
+// Lattices without interior solids, FREESLIP or PRESSURE faces run the
+// general kernel compiled without their rules. The even step touches only
+// each node's own slots, which no other node reads: solid nodes may run it
+// (their populations are never read) and free slip has no even-step rule,
+// so there the rules are compiled in only for PRESSURE faces.
+template <int KIND, typename S>
+void step_model(const lbm_lattice* L, bool odd, long long t, void* rec) {
+  const bool ext = odd ? (L->solids || L->args.bc.freeslip || L->args.bc.pressure)
+                       : L->args.bc.pressure != 0;
+  const bool nt = odd ? L->nt_odd : L->nt_even;
+  if constexpr (std::is_same_v<S, _Float16>) {
+    // FP16 even steps: two nodes per lane
+    if (!odd && !ext && rec == nullptr && L->N % 2 == 0) {
+      const dim3 block(256), grid((unsigned)((L->N / 2 + 255) / 256));
+      const bool by_xcd = L->rows_all.by_xcd;
+      TraceScope ts(L->tracer.get(), L->stream,
+                    L->has_bc ? "step_even_pair_kernel (FP16, boundaries)"
+                              : "step_even_pair_kernel (FP16)");
+      auto go = [&](auto bc_c, auto nt_c) {
+        hipLaunchKernelGGL((step_even_pair_kernel<KIND, decltype(bc_c)::value,
+                                                  decltype(nt_c)::value>),
+                           grid, block, 0, L->stream, L->args, by_xcd);
+      };
+      auto by_bc = [&](auto nt_c) {
+        if (L->has_bc) go(std::true_type{}, nt_c);
+        else go(std::false_type{}, nt_c);
+      };
+      if (nt) by_bc(std::true_type{});
+      else by_bc(std::false_type{});
+      return;
+    }
+  }
+  auto by_nt = [&](auto ext_c) {
+    if (nt)
+      step_model_ext<KIND, S, decltype(ext_c)::value, true>(L, odd, t, rec);
+    else
+      step_model_ext<KIND, S, decltype(ext_c)::value, false>(L, odd, t, rec);
+  };
+  if (ext) by_nt(std::true_type{});
+  else by_nt(std::false_type{});
+}
+
+// Runs fn<KIND, BC>() for the lattice's model.
+template <typename Fn>
+void with_model(const lbm_lattice* L, Fn&& fn) {
+  auto by_bc = [&](auto kind_c) {
+    if (L->has_bc)
+      fn(kind_c, std::true_type{});
+    else
+      fn(kind_c, std::false_type{});
+  };
+  switch (L->kind) {
+    case 0: by_bc(std::integral_constant<int, 0>{}); break;
+    case 1: by_bc(std::integral_constant<int, 1>{}); break;
+    case 3: by_bc(std::integral_constant<int, 3>{}); break;
+    default: by_bc(std::integral_constant<int, 2>{}); break;
+  }
+}
+
+// Runs fn(a value of the field type).
+template <typename Fn>
+void with_field(bool f64, Fn&& fn) {
+  if (f64)
+    fn(double());
+  else
+    fn(float());
+}
+
+}  // namespace
+
+namespace lbm {
+
+template <typename S>
+void Ops<S>::step(const lbm_lattice* L, bool odd, long long t, void* rec) {
+  switch (L->kind) {
+    case 0: step_model<0, S>(L, odd, t, rec); break;
+    case 1: step_model<1, S>(L, odd, t, rec); break;
+    case 3: step_model<3, S>(L, odd, t, rec); break;
+    default: step_model<2, S>(L, odd, t, rec); break;
+  }
+}
+
+// Interpolated bounce-back over the link list after a step.
+template <typename S>
+void Ops<S>::links(const lbm_lattice* L, bool after_odd) {
+  const dim3 grid((unsigned)((L->nlinks + 7) / 8)), block(256);  // 32 lanes per node
+  TraceScope ts(L->tracer.get(), L->stream, "link_kernel (interpolated bounce-back)");
+  auto go = [&](auto q_c, auto odd_c) {
+    constexpr int Q = decltype(q_c)::value;
+    constexpr bool ODD = decltype(odd_c)::value;
+    hipLaunchKernelGGL((link_kernel<Q, S, ODD>), grid, block, 0, L->stream, L->args,
+                       L->link_nodes, L->link_q, L->nlinks);
+  };
+  if (L->Q == 27) {
+    if (after_odd) go(std::integral_constant<int, 27>{}, std::true_type{});
+    else go(std::integral_constant<int, 27>{}, std::false_type{});
+  } else {
+    if (after_odd) go(std::integral_constant<int, 19>{}, std::true_type{});
+    else go(std::integral_constant<int, 19>{}, std::false_type{});
+  }
+}
+
+template <typename S>
+void Ops<S>::init_equilibrium(const lbm_lattice* L, const void* drho, const void* u, bool f64) {
+  with_model(L, [&](auto kind_c, auto) {
+    constexpr int KIND = decltype(kind_c)::value;
+    with_field(f64, [&](auto v) {
+      using O = decltype(v);
+      hipLaunchKernelGGL((init_equilibrium_kernel<KIND, S, O>), L->grid, L->block, 0, L->stream,
+                         L->args, (const O*)drho, (const O*)u);
+    });
+  });
+}
+
+template <typename S>
+void Ops<S>::set_populations(const lbm_lattice* L, const void* f, bool f64) {
+  with_field(f64, [&](auto v) {
+    using O = decltype(v);
+    if (L->Q == 27)
+      hipLaunchKernelGGL((set_populations_kernel<27, S, O>), L->grid, L->block, 0, L->stream,
+                         L->args, (const O*)f);
+    else
+      hipLaunchKernelGGL((set_populations_kernel<19, S, O>), L->grid, L->block, 0, L->stream,
+                         L->args, (const O*)f);
+  });
+}
+
+template <typename S>
+void Ops<S>::get_populations(const lbm_lattice* L, void* f, bool f64) {
+  auto go = [&](auto q_c, auto bc_c) {
+    constexpr int Q = decltype(q_c)::value;
+    constexpr bool BC = decltype(bc_c)::value;
+    with_field(f64, [&](auto v) {
+      using O = decltype(v);
+      hipLaunchKernelGGL((get_populations_kernel<Q, S, BC, O>), L->grid, L->block, 0, L->stream,
+                         L->args, L->parity, (long long)L->t, (O*)f);
+    });
+  };
+  auto by_bc = [&](auto q_c) {
+    if (L->has_bc) go(q_c, std::true_type{});
+    else go(q_c, std::false_type{});
+  };
+  if (L->Q == 27) by_bc(std::integral_constant<int, 27>{});
+  else by_bc(std::integral_constant<int, 19>{});
+}
+
+template <typename S>
+void Ops<S>::macroscopic(const lbm_lattice* L, void* rho, void* u, bool f64, int rho_mode) {
+  with_model(L, [&](auto kind_c, auto bc_c) {
+    constexpr int KIND = decltype(kind_c)::value;
+    constexpr bool BC = decltype(bc_c)::value;
+    with_field(f64, [&](auto v) {
+      using O = decltype(v);
+      hipLaunchKernelGGL((macroscopic_kernel<KIND, S, BC, O>), L->grid, L->block, 0, L->stream,
+                         L->args, L->parity, (long long)L->t, (O*)rho, (O*)u, rho_mode);
+    });
+  });
+}
+
+template <typename S>
+void Ops<S>::stats_accumulate(const lbm_lattice* L, double* sums) {
+  with_model(L, [&](auto kind_c, auto bc_c) {
+    constexpr int KIND = decltype(kind_c)::value;
+    constexpr bool BC = decltype(bc_c)::value;
+    hipLaunchKernelGGL((stats_accumulate_kernel<KIND, S, BC>), L->grid, L->block, 0, L->stream,
+                       L->args, L->parity, (long long)L->t, sums);
+  });
+}
+
+template <typename S>
+void Ops<S>::reduce_partial(const lbm_lattice* L, dim3 grid, double* partial) {
+  with_model(L, [&](auto kind_c, auto bc_c) {
+    constexpr int KIND = decltype(kind_c)::value;
+    constexpr bool BC = decltype(bc_c)::value;
+    hipLaunchKernelGGL((reduce_partial_kernel<KIND, S, BC>), grid, L->block, 0, L->stream, L->args,
+                       L->parity, (long long)L->t, partial);
+  });
+}
+
+template <typename S>
+void Ops<S>::probe(const lbm_lattice* L, int3 lo, int3 hi, double scale, void* lambda, bool f64,
+                   double* partial) {
+  with_model(L, [&](auto kind_c, auto bc_c) {
+    constexpr int KIND = decltype(kind_c)::value;
+    constexpr bool BC = decltype(bc_c)::value;
+    with_field(f64, [&](auto v) {
+      using O = decltype(v);
+      hipLaunchKernelGGL((probe_kernel<KIND, S, BC, O>), L->grid, L->block, 0, L->stream, L->args,
+                         L->parity, (long long)L->t, lo, hi, scale, (O*)lambda, partial);
+    });
+  });
+}
+
+template struct Ops<LBM_STORAGE>;
+
+}  // namespace lbm
