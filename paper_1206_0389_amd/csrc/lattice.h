@@ -40,6 +40,7 @@ struct lbm_lattice {
   lbm::Rows rows_all, rows_inner, rows_bnd;
   dim3 grid_inner, grid_bnd, block_bnd;
   unsigned tiles_all = 0, tiles_inner = 0;  // workgroups of 256 nodes (FLAT)
+  bool resident = false;  // populations fit the last-level cache
   // Streaming hint of the steps (see ld): on lattices larger than the
   // last-level cache, where populations (even steps, which run over them from
   // end to end) or rows (odd steps) are whole memory lines.

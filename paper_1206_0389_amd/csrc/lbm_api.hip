@@ -65,15 +65,16 @@ void plan_rows(lbm_lattice* L) {
   // with walls), 96x112x224 MRT FP32 (183 MB): 54.0 / 56.5 us against 74.5 /
   // 67.4 with the hint in launch order. Beyond it the eight far apart ranges
   // cost more than the shared lines (256x256x512 FCLB FP32, 3.6 GB: 1296 /
-  // 1514 against 1251 / 1396 us) and the hint pays (1251 against 1351 us),
+  // 1514 against 1251 / 1396 us; all at five workgroups per CU) and the hint
+  // pays (1251 against 1351 us),
   // where the accesses are whole lines: odd steps on 190-node rows (1.0 GB)
   // 440 us with it, 413 without; their even steps, whose slabs are aligned,
   // 361 and 393.
   const double bytes = (double)L->N * L->Q * (double)L->elem;
-  const bool resident = bytes <= 256.0 * 1048576.0;
-  all.by_xcd = resident;
-  L->nt_even = !resident && (L->N * L->elem) % 128 == 0;
-  L->nt_odd = !resident && ((size_t)nx * L->elem) % 128 == 0;
+  L->resident = bytes <= 256.0 * 1048576.0;
+  all.by_xcd = L->resident;
+  L->nt_even = !L->resident && (L->N * L->elem) % 128 == 0;
+  L->nt_odd = !L->resident && ((size_t)nx * L->elem) % 128 == 0;
   L->tiles_all = (unsigned)((L->N + 255) / 256);
   L->rows_all = all;
   const bool znp = (np & 48u) != 0;

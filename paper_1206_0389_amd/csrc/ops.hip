@@ -14,11 +14,30 @@ using namespace lbm;
 
 namespace {
 
+// LDS requested by a step's workgroups beyond the last-level cache, only to
+// limit how many run on a CU (160 KB). These steps are bound by HBM, two
+// workgroups per CU already keep it busy, and the fewer nodes are in flight
+// the fewer DRAM pages are open at once. FP32 256x256x512 by workgroups per
+// CU 5 (registers) / 3 / 2, us: FCLB even 1274 / 1227 / 1185, odd 1361 / 1326
+// / 1276, odd with walls 1381 / 1368 / 1499 (their address arithmetic needs
+// the third); MRT even 863 / 825 / 849, odd 926 / 866 / 862, with walls 932 /
+// 916 / 933. FP64 256^3: FCLB even 1282 / 1280 / 1246, odd 1408 / 1390 / 1365,
+// with walls 1400 / 1386 / 1383; MRT 859 / 857 / 836, 949 / 940 / 920, 970 /
+// 960 / 939. FP16 is bound by arithmetic: none (FCLB even 607 / 605 / 768, odd
+// with walls 763 / 864 / 1152). Within the last-level cache nothing is gained.
+template <int KIND, typename S, bool WALLS>
+unsigned lds_limit(const lbm_lattice* L) {
+  if (std::is_same_v<S, _Float16> || L->resident) return 0;
+  const bool two = std::is_same_v<S, double> || (KIND >= 2 && !WALLS);
+  return (two ? 64u : 52u) * 1024u;
+}
+
 template <int KIND, typename S, bool ODD, int BCM, int ROWS, bool EXT, bool NT>
 void launch_step(const lbm_lattice* L, dim3 grid, dim3 block, const Rows& r, long long t,
                  void* rec) {
   TraceScope ts(L->tracer.get(), L->stream, LBM_TRACE_LABEL("step_kernel"));
-  hipLaunchKernelGGL((step_kernel<KIND, S, ODD, BCM, ROWS, EXT, NT>), grid, block, 0, L->stream,
+  hipLaunchKernelGGL((step_kernel<KIND, S, ODD, BCM, ROWS, EXT, NT>), grid, block,
+                     (ROWS == ROWS_FLAT ? lds_limit<KIND, S, BCM == BC_WALLS>(L) : 0u), L->stream,
                      L->args, r, t, (typename Compute<S>::type*)rec);
 }
 
