@@ -890,6 +890,85 @@ __device__ __forceinline__ void fetch_natural(const LatArgs& a, const Node& n, i
   }
 }
 
+// What a readout kernel covers and how: rows (FLAT, all nodes), the time, and
+// the faces whose nodes need the general pull at odd parity (ALL_GENERAL: all
+// of them take it, where the wall rules' offsets would not fit).
+constexpr uint32_t ALL_GENERAL = 1u << 31;
+struct ReadArgs {
+  Rows rows;
+  long long t;
+  uint32_t general;
+};
+
+// fetch_natural of node i of the FLAT order for the readout kernels. Even
+// parity needs no coordinates. At odd parity waves off the faces in
+// r.general read like wall rows, the others by the general rules: those
+// select between up to four addresses per population, ten times the
+// arithmetic (100x75x110 CLB FP64, sums of all nodes at odd parity: 139 us
+// with the general rules everywhere and a workgroup for every row or two,
+// 45 us so; populations 92 and 62 us).
+template <int Q, typename S, bool ODD, bool BC, bool NT>
+__device__ __forceinline__ void read_node(const LatArgs& a, const ReadArgs& r, uint32_t i,
+                                          double (&f)[Q]) {
+  const S* F = (const S*)a.f;
+  const size_t N = (size_t)a.N;
+  uint32_t sb = 0;
+  if constexpr (BC) {
+    if (a.solid_nb) sb = a.solid_nb[i];
+  }
+  if constexpr (!ODD) {
+    static_for<0, Q>([&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      f[I] = ldo<double, NT>(F + (size_t)I * N, i * (uint32_t)sizeof(S));
+    });
+  } else {
+    const uint32_t row = r.rows.by_nx(i), pl = r.rows.by_ny(row);
+    const Node n = make_node(a, (int)(i - row * (uint32_t)a.nx),
+                             (int)(row - pl * (uint32_t)a.ny), (int)pl);
+    if constexpr (!BC) {
+      static_for<0, Q>([&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        f[I] = ldo<double>(F + (size_t)opposite<Q>(I) * N,
+                           (uint32_t)n.at(-cx(I), -cy(I), -cz(I)) * (uint32_t)sizeof(S));
+      });
+    } else if (__builtin_amdgcn_ballot_w64((n.atface & r.general) != 0 ||
+                                           r.general == ALL_GENERAL) == 0) {
+      static_for<0, Q>([&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        f[I] = pull_walls<Q, I, double, false, true>(a, F, n, sb);
+      });
+    } else {
+      double uin[3] = {0, 0, 0};
+      if (n.atface & a.bc.inlet) inlet_velocity(a.bc, n.x, n.y, n.z, r.t - 1, uin);
+      static_for<0, Q>([&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        f[I] = ld<double>(pull_addr<Q, I, S, BC>(a, F, n, sb)) +
+               pull_term<Q, I, double>(a.bc, n.atface, uin);
+      });
+    }
+  }
+  if constexpr (BC) {
+    if (sb >> 31) {
+#pragma unroll
+      for (int k = 0; k < Q; ++k) f[k] = 0.0;
+    }
+  }
+}
+
+// Density deviation and momentum.
+template <int Q>
+__device__ __forceinline__ void moments(const double (&f)[Q], double& d, double (&j)[3]) {
+  d = 0;
+  j[0] = j[1] = j[2] = 0;
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    d += f[i];
+    j[0] += cx(i) * f[i];
+    j[1] += cy(i) * f[i];
+    j[2] += cz(i) * f[i];
+  }
+}
+
 // Solid-neighbour masks of the nodes (LatArgs::solid_nb) from a solid flag
 // per node; flag[0] := 1 if a solid node lies on an OUTFLOW face (the
 // outflow copy would read it).
@@ -975,15 +1054,51 @@ __global__ __launch_bounds__(256) void link_kernel(const LatArgs a, const int32_
   if (link) st(F + (size_t)ko * N + self, v);
 }
 
+// Even parity: the slabs one after the other, G of them and U nodes 256 apart
+// per lane (8 in flight saturate HBM; a lane for all populations of a node
+// keeps 2 Q streams open and reached 1433 us instead of 1199 for 256x256x512
+// FCLB FP32 to FP32, 173 instead of 139 for 128x128x256, 65 instead of 50 for
+// 131x97x111 within the last-level cache). FP16: nine slabs, one node
+// (954 us, against 1567 for one slab and eight nodes). SOLID: three slabs and
+// two nodes, as the mask is read once per group (152 us; 183 us by single
+// slabs, 173 us for all at once).
+template <typename S, bool SOLID, typename O, int G, int U, bool NT>
+__global__ __launch_bounds__(256) void get_slabs_kernel(const LatArgs a, O* out) {
+  const size_t N = (size_t)a.N, q0 = (size_t)blockIdx.y * G;
+  const S* __restrict__ F = (const S*)a.f + q0 * N;
+  out += q0 * N;
+  const uint32_t i0 = blockIdx.x * (256u * U) + threadIdx.x;
+  S v[U][G];
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const uint32_t i = i0 + 256u * k;
+    if (i < N) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) v[k][g] = ld<S, NT>(F + g * N + i);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const uint32_t i = i0 + 256u * k;
+    if (i < N) {
+      bool solid = false;
+      if constexpr (SOLID) solid = a.solid_nb[i] >> 31;
+#pragma unroll
+      for (int g = 0; g < G; ++g) st<true>(out + g * N + i, solid ? O(0) : O((double)v[k][g]));
+    }
+  }
+}
+
+// Odd parity: a node per lane.
 template <int Q, typename S, bool BC, typename O>
-__global__ __launch_bounds__(256) void get_populations_kernel(const LatArgs a, int parity,
-                                                              long long t, O* out) {
-  int x, y, z;
-  if (!node_coords(a, x, y, z)) return;
-  const Node n = make_node(a, x, y, z);
+__global__ __launch_bounds__(256) void get_populations_kernel(const LatArgs a, const ReadArgs r,
+                                                              O* out) {
+  const uint32_t i = xcd_tile(r.rows.by_xcd) * 256u + threadIdx.x;
+  if (i >= r.rows.n1) return;
   double f[Q];
-  fetch_natural<Q, S, BC>(a, n, parity, t, f);
-  for (int i = 0; i < Q; ++i) out[(size_t)i * a.N + n.self] = O(f[i]);
+  read_node<Q, S, true, BC, false>(a, r, i, f);
+#pragma unroll
+  for (int k = 0; k < Q; ++k) st<true>(out + (size_t)k * a.N + i, O(f[k]));
 }
 
 template <int Q, typename S, typename O>
@@ -1045,29 +1160,20 @@ __global__ __launch_bounds__(256) void init_equilibrium_kernel(const LatArgs a, 
   }
 }
 
-template <int KIND, typename S, bool BC, typename O>
-__global__ __launch_bounds__(256) void macroscopic_kernel(const LatArgs a, int parity, long long t,
+template <int Q, typename S, bool ODD, bool BC, typename O, bool NT>
+__global__ __launch_bounds__(256) void macroscopic_kernel(const LatArgs a, const ReadArgs r,
                                                           O* rho, O* u, int rho_mode) {
-  constexpr int Q = Model<KIND>::Q;
-  int x, y, z;
-  if (!node_coords(a, x, y, z)) return;
-  const Node n = make_node(a, x, y, z);
-  double f[Q];
-  fetch_natural<Q, S, BC>(a, n, parity, t, f);
-  double d = 0, j[3] = {0, 0, 0};
-  for (int i = 0; i < Q; ++i) {
-    d += f[i];
-    j[0] += cx(i) * f[i];
-    j[1] += cy(i) * f[i];
-    j[2] += cz(i) * f[i];
-  }
-  const double r = (Model<KIND>::Q == 27) ? 1.0 + d : 1.0;
-  if (rho) rho[n.self] = O(rho_mode == 0 ? 1.0 + d : d);
+  const uint32_t i = xcd_tile(r.rows.by_xcd) * 256u + threadIdx.x;
+  if (i >= r.rows.n1) return;
+  double f[Q], d, j[3];
+  read_node<Q, S, ODD, BC, NT>(a, r, i, f);
+  moments<Q>(f, d, j);
+  const double m = Q == 27 ? 1.0 + d : 1.0;
+  if (rho) st<true>(rho + i, O(rho_mode == 0 ? 1.0 + d : d));
   if (u) {
     const size_t N = (size_t)a.N;
-    u[n.self] = O(j[0] / r);
-    u[N + n.self] = O(j[1] / r);
-    u[2 * N + n.self] = O(j[2] / r);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) st<true>(u + c * N + i, O(j[c] / m));
   }
 }
 
@@ -1075,32 +1181,25 @@ __global__ __launch_bounds__(256) void macroscopic_kernel(const LatArgs a, int p
 // Section 3: mean velocity and the turbulent intensity of Eq. (25)): adds u
 // and the squares u_a^2 of the current natural state (u as in
 // macroscopic_kernel) to sums [6][N] in FP64; each node owns its entries.
-template <int KIND, typename S, bool BC>
-__global__ __launch_bounds__(256) void stats_accumulate_kernel(const LatArgs a, int parity,
-                                                               long long t, double* sums) {
-  constexpr int Q = Model<KIND>::Q;
-  int x, y, z;
-  if (!node_coords(a, x, y, z)) return;
-  const Node n = make_node(a, x, y, z);
-  double f[Q];
-  fetch_natural<Q, S, BC>(a, n, parity, t, f);
-  double d = 0, j[3] = {0, 0, 0};
-  for (int i = 0; i < Q; ++i) {
-    d += f[i];
-    j[0] += cx(i) * f[i];
-    j[1] += cy(i) * f[i];
-    j[2] += cz(i) * f[i];
-  }
-  const double r = (Model<KIND>::Q == 27) ? 1.0 + d : 1.0;
+template <int Q, typename S, bool ODD, bool BC, bool NT>
+__global__ __launch_bounds__(256) void stats_accumulate_kernel(const LatArgs a, const ReadArgs r,
+                                                               double* sums) {
+  const uint32_t i = xcd_tile(r.rows.by_xcd) * 256u + threadIdx.x;
+  if (i >= r.rows.n1) return;
   const size_t N = (size_t)a.N;
   // the running sums are streamed once per call (non-temporal hint)
+  double s[6];
+#pragma unroll
+  for (int c = 0; c < 6; ++c) s[c] = ld<double, true>(sums + c * N + i);
+  double f[Q], d, j[3];
+  read_node<Q, S, ODD, BC, NT>(a, r, i, f);
+  moments<Q>(f, d, j);
+  const double m = Q == 27 ? 1.0 + d : 1.0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const double u = j[c] / r;
-    double* s1 = sums + c * N + n.self;
-    double* s2 = sums + (3 + c) * N + n.self;
-    st<true>(s1, ld<double, true>(s1) + u);
-    st<true>(s2, ld<double, true>(s2) + u * u);
+    const double u = j[c] / m;
+    st<true>(sums + c * N + i, s[c] + u);
+    st<true>(sums + (3 + c) * N + i, s[3 + c] + u * u);
   }
 }
 
@@ -1138,48 +1237,37 @@ __global__ __launch_bounds__(256) void stats_finalize_kernel(const LatArgs a, co
 }
 
 // Per-block FP64 partial sums (mass deviation, momentum, kinetic energy) in
-// a fixed tree order, one row of 5 per block of the launch grid.
-template <int KIND, typename S, bool BC>
-__global__ __launch_bounds__(256) void reduce_partial_kernel(const LatArgs a, int parity,
-                                                             long long t, double* partial) {
-  constexpr int Q = Model<KIND>::Q;
+// a fixed order, one row of 5 per block: a lane adds its nodes of every
+// gridDim-th tile, then the block's lanes are added in a tree.
+template <int Q, typename S, bool ODD, bool BC, bool NT>
+__global__ __launch_bounds__(256) void reduce_partial_kernel(const LatArgs a, const ReadArgs r,
+                                                             double* partial) {
   __shared__ double sh[5][256];
-  const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-  const int nthreads = blockDim.x * blockDim.y;
+  const int tid = threadIdx.x;
+  const uint32_t n1 = r.rows.n1, tiles = (n1 + 255u) / 256u;
   double v[5] = {0, 0, 0, 0, 0};
-  int x, y, z;
-  // a block sums the planes z = blockIdx.z + k gridDim.z (one plane when the
-  // grid spans every plane)
-  if (node_coords(a, x, y, z)) {
-    for (; z < a.nz; z += gridDim.z) {
-      const Node n = make_node(a, x, y, z);
-      double f[Q];
-      fetch_natural<Q, S, BC>(a, n, parity, t, f);
-      double d = 0, j[3] = {0, 0, 0};
-      for (int i = 0; i < Q; ++i) {
-        d += f[i];
-        j[0] += cx(i) * f[i];
-        j[1] += cy(i) * f[i];
-        j[2] += cz(i) * f[i];
-      }
-      const double r = (Model<KIND>::Q == 27) ? 1.0 + d : 1.0;
-      v[0] += d;
-      v[1] += j[0];
-      v[2] += j[1];
-      v[3] += j[2];
-      v[4] += 0.5 * (j[0] * j[0] + j[1] * j[1] + j[2] * j[2]) / r;
-    }
+  for (uint32_t tile = xcd_tile(r.rows.by_xcd); tile < tiles; tile += gridDim.x) {
+    const uint32_t i = tile * 256u + tid;
+    if (i >= n1) break;
+    double f[Q], d, j[3];
+    read_node<Q, S, ODD, BC, NT>(a, r, i, f);
+    moments<Q>(f, d, j);
+    const double m = Q == 27 ? 1.0 + d : 1.0;
+    v[0] += d;
+    v[1] += j[0];
+    v[2] += j[1];
+    v[3] += j[2];
+    v[4] += 0.5 * (j[0] * j[0] + j[1] * j[1] + j[2] * j[2]) / m;
   }
   for (int k = 0; k < 5; ++k) sh[k][tid] = v[k];
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s && tid + s < nthreads)
+    if (tid < s)
       for (int k = 0; k < 5; ++k) sh[k][tid] += sh[k][tid + s];
     __syncthreads();
   }
   if (tid == 0) {
-    const size_t b = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    for (int k = 0; k < 5; ++k) partial[b * 5 + k] = sh[k][0];
+    for (int k = 0; k < 5; ++k) partial[(size_t)blockIdx.x * 5 + k] = sh[k][0];
   }
 }
 

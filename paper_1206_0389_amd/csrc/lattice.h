@@ -64,7 +64,7 @@ struct Ops {
   static void get_populations(const lbm_lattice* L, void* f, bool f64);
   static void macroscopic(const lbm_lattice* L, void* rho, void* u, bool f64, int rho_mode);
   static void stats_accumulate(const lbm_lattice* L, double* sums);
-  static void reduce_partial(const lbm_lattice* L, dim3 grid, double* partial);
+  static void reduce_partial(const lbm_lattice* L, unsigned blocks, double* partial);
   static void probe(const lbm_lattice* L, int3 lo, int3 hi, double scale, void* lambda, bool f64,
                     double* partial);
 };

@@ -146,15 +146,22 @@ void default_bc(BcArgs& b) {
   b.ghost_n = 1;
 }
 
+// Blocks of a reduction: as many as run at once, each summing several tiles,
+// so that the single block that adds up their rows has little to do.
+unsigned reduce_blocks(const lbm_lattice* L) {
+  return L->tiles_all < 1024u ? L->tiles_all : 1024u;
+}
+
 // FP64 sums of the current state (lbm_reduce's definition), blocking.
 int reduce_now(lbm_lattice* L, double out[5]) {
   double* partial = (double*)(L->base + L->off_partial);
   double* result = (double*)(L->base + L->off_result);
   {
     TraceScope ts(L->tracer.get(), L->stream, "reduce_partial_kernel + reduce_final_kernel");
-    by_storage(L, [&](auto s) { Ops<decltype(s)>::reduce_partial(L, L->grid, partial); });
+    const unsigned nb = reduce_blocks(L);
+    by_storage(L, [&](auto s) { Ops<decltype(s)>::reduce_partial(L, nb, partial); });
     hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(256), 0, L->stream, partial,
-                       L->nblocks, result);
+                       (size_t)nb, result);
   }
   const int rc = check_launch();
   if (rc) return rc;
@@ -619,20 +626,17 @@ int lbm_set_check(lbm_lattice* L, int64_t every, double mass_tol) {
 int lbm_reduce_static(lbm_lattice* L, double* out) {
   if (!L || !out) return LBM_EINVAL;
   if (!L->base) return LBM_EUNBOUND;
-  // fold z planes into the blocks of one plane so the partials fit
   const size_t plane = (size_t)L->grid.x * L->grid.y;
   if (plane > kStaticPartials) return LBM_EINVAL;
   double* partial = nullptr;
   int rc = static_scratch(L->stream, &partial);
   if (rc) return rc;
-  size_t gz = kStaticPartials / plane;
-  if (gz > (size_t)L->grid.z) gz = L->grid.z;
-  const dim3 grid(L->grid.x, L->grid.y, (unsigned)gz);
-  by_storage(L, [&](auto s) { Ops<decltype(s)>::reduce_partial(L, grid, partial); });
+  const unsigned nb = reduce_blocks(L);
+  by_storage(L, [&](auto s) { Ops<decltype(s)>::reduce_partial(L, nb, partial); });
   rc = check_launch();
   if (rc) return rc;
   hipLaunchKernelGGL(reduce_final_kernel, dim3(1), dim3(256), 0, L->stream, partial,
-                     plane * gz, out);
+                     (size_t)nb, out);
   return check_launch();
 }
 

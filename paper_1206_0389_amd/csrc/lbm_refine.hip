@@ -1215,17 +1215,16 @@ int lbm_refined_get_populations(lbm_refined* R, int level, void* f, int dtype) {
   if (!R->base) return LBM_EUNBOUND;
   if (R->lev[level].Nbox == 0) return LBM_OK;
   const LatArgs a = level_view(R, level);
-  dim3 grid, block;
-  view_launch(a, grid, block);
+  const unsigned tiles = (unsigned)(((size_t)a.N + 255) / 256);
   with_kind_s(R, [&](auto kc, auto st_) {
     constexpr int Q = Model<decltype(kc)::value>::Q;
     using S = typename decltype(st_)::type;
     if (dtype == LBM_DTYPE_F64)
-      hipLaunchKernelGGL((get_populations_kernel<Q, S, false, double>), grid, block, 0, R->stream,
-                         a, 0, 0LL, (double*)f);
+      hipLaunchKernelGGL((get_slabs_kernel<S, false, double, Q, 1, false>), dim3(tiles),
+                         dim3(256), 0, R->stream, a, (double*)f);
     else
-      hipLaunchKernelGGL((get_populations_kernel<Q, S, false, float>), grid, block, 0, R->stream,
-                         a, 0, 0LL, (float*)f);
+      hipLaunchKernelGGL((get_slabs_kernel<S, false, float, Q, 1, false>), dim3(tiles),
+                         dim3(256), 0, R->stream, a, (float*)f);
   });
   return check_launch();
 }
@@ -1237,17 +1236,18 @@ int lbm_refined_get_macroscopic(lbm_refined* R, int level, void* rho, void* u, i
   if (!R->base) return LBM_EUNBOUND;
   if ((!rho && !u) || R->lev[level].Nbox == 0) return LBM_OK;
   const LatArgs a = level_view(R, level);
-  dim3 grid, block;
-  view_launch(a, grid, block);
+  ReadArgs r{};
+  r.rows.n1 = (uint32_t)a.N;
+  const unsigned tiles = (unsigned)(((size_t)a.N + 255) / 256);
   with_kind_s(R, [&](auto kc, auto st_) {
-    constexpr int KIND = decltype(kc)::value;
+    constexpr int Q = Model<decltype(kc)::value>::Q;
     using S = typename decltype(st_)::type;
     if (dtype == LBM_DTYPE_F64)
-      hipLaunchKernelGGL((macroscopic_kernel<KIND, S, false, double>), grid, block, 0, R->stream,
-                         a, 0, 0LL, (double*)rho, (double*)u, rho_mode);
+      hipLaunchKernelGGL((macroscopic_kernel<Q, S, false, false, double, false>), dim3(tiles),
+                         dim3(256), 0, R->stream, a, r, (double*)rho, (double*)u, rho_mode);
     else
-      hipLaunchKernelGGL((macroscopic_kernel<KIND, S, false, float>), grid, block, 0, R->stream, a,
-                         0, 0LL, (float*)rho, (float*)u, rho_mode);
+      hipLaunchKernelGGL((macroscopic_kernel<Q, S, false, false, float, false>), dim3(tiles),
+                         dim3(256), 0, R->stream, a, r, (float*)rho, (float*)u, rho_mode);
   });
   return check_launch();
 }

@@ -24,10 +24,11 @@ namespace {
 // 916 / 933. FP64 256^3: FCLB even 1282 / 1280 / 1246, odd 1408 / 1390 / 1365,
 // with walls 1400 / 1386 / 1383; MRT 859 / 857 / 836, 949 / 940 / 920, 970 /
 // 960 / 939. FP16 is bound by arithmetic: none (FCLB even 607 / 605 / 768, odd
-// with walls 763 / 864 / 1152). Within the last-level cache nothing is gained.
-template <int KIND, typename S, bool WALLS>
+// with walls 763 / 864 / 1152), and so are wall rows with solids (128x128x256
+// FCLB FP32 159 / 178 us). Within the last-level cache nothing is gained.
+template <int KIND, typename S, bool WALLS, bool SOLID>
 unsigned lds_limit(const lbm_lattice* L) {
-  if (std::is_same_v<S, _Float16> || L->resident) return 0;
+  if (std::is_same_v<S, _Float16> || L->resident || (WALLS && SOLID)) return 0;
   const bool two = std::is_same_v<S, double> || (KIND >= 2 && !WALLS);
   return (two ? 64u : 52u) * 1024u;
 }
@@ -37,7 +38,7 @@ void launch_step(const lbm_lattice* L, dim3 grid, dim3 block, const Rows& r, lon
                  void* rec) {
   TraceScope ts(L->tracer.get(), L->stream, LBM_TRACE_LABEL("step_kernel"));
   hipLaunchKernelGGL((step_kernel<KIND, S, ODD, BCM, ROWS, EXT, NT>), grid, block,
-                     (ROWS == ROWS_FLAT ? lds_limit<KIND, S, BCM == BC_WALLS>(L) : 0u), L->stream,
+                     (ROWS == ROWS_FLAT ? lds_limit<KIND, S, BCM == BC_WALLS, EXT>(L) : 0u), L->stream,
                      L->args, r, t, (typename Compute<S>::type*)rec);
 }
 
@@ -143,6 +144,39 @@ void with_field(bool f64, Fn&& fn) {
     fn(float());
 }
 
+// Runs fn(Q, odd parity, boundaries, streaming hint, ReadArgs) for a readout.
+// The hint at even parity, whose accesses run from end to end, on lattices
+// that the last-level cache does not hold (as for the steps). Workgroups per
+// CU are not limited here: fewer cost (256x256x512 FCLB FP16, density and
+// velocity: 382 us; 455 us with three).
+template <typename Fn>
+void with_read(const lbm_lattice* L, Fn&& fn) {
+  ReadArgs r;
+  r.rows = L->rows_all;
+  r.t = (long long)L->t;
+  const BcArgs& bc = L->args.bc;
+  r.general = L->split_odd ? bc.nonper & ~(bc.wall & 15u) : ALL_GENERAL;
+  auto go = [&](auto q_c, auto odd_c, auto bc_c) {
+    if constexpr (!decltype(odd_c)::value) {
+      if (!L->resident) {
+        fn(q_c, odd_c, bc_c, std::true_type{}, r);
+        return;
+      }
+    }
+    fn(q_c, odd_c, bc_c, std::false_type{}, r);
+  };
+  auto by_bc = [&](auto q_c, auto odd_c) {
+    if (L->has_bc) go(q_c, odd_c, std::true_type{});
+    else go(q_c, odd_c, std::false_type{});
+  };
+  auto by_parity = [&](auto q_c) {
+    if (L->parity) by_bc(q_c, std::true_type{});
+    else by_bc(q_c, std::false_type{});
+  };
+  if (L->Q == 27) by_parity(std::integral_constant<int, 27>{});
+  else by_parity(std::integral_constant<int, 19>{});
+}
+
 }  // namespace
 
 namespace lbm {
@@ -204,53 +238,63 @@ void Ops<S>::set_populations(const lbm_lattice* L, const void* f, bool f64) {
 
 template <typename S>
 void Ops<S>::get_populations(const lbm_lattice* L, void* f, bool f64) {
-  auto go = [&](auto q_c, auto bc_c) {
+  with_read(L, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
     constexpr int Q = decltype(q_c)::value;
-    constexpr bool BC = decltype(bc_c)::value;
+    constexpr bool BC = decltype(bc_c)::value, NT = decltype(nt_c)::value;
     with_field(f64, [&](auto v) {
       using O = decltype(v);
-      hipLaunchKernelGGL((get_populations_kernel<Q, S, BC, O>), L->grid, L->block, 0, L->stream,
-                         L->args, L->parity, (long long)L->t, (O*)f);
+      if constexpr (decltype(odd_c)::value) {
+        hipLaunchKernelGGL((get_populations_kernel<Q, S, BC, O>), dim3(L->tiles_all), dim3(256),
+                           0, L->stream, L->args, r, (O*)f);
+      } else {
+        auto go = [&](auto solid_c) {
+          constexpr bool HALF = std::is_same_v<S, _Float16>, SOLID = decltype(solid_c)::value;
+          constexpr int G = HALF || (SOLID && Q == 19) ? (Q == 27 ? 9 : 19) : (SOLID ? 3 : 1);
+          constexpr int U = HALF || G > 3 ? 1 : (SOLID ? 2 : (NT ? 8 : 4));
+          const dim3 grid((unsigned)((L->N + 256 * U - 1) / (256 * U)), Q / G);
+          hipLaunchKernelGGL((get_slabs_kernel<S, SOLID, O, G, U, NT>), grid, dim3(256), 0,
+                             L->stream, L->args, (O*)f);
+        };
+        if constexpr (BC) {
+          if (L->solids) {
+            go(std::true_type{});
+            return;
+          }
+        }
+        go(std::false_type{});
+      }
     });
-  };
-  auto by_bc = [&](auto q_c) {
-    if (L->has_bc) go(q_c, std::true_type{});
-    else go(q_c, std::false_type{});
-  };
-  if (L->Q == 27) by_bc(std::integral_constant<int, 27>{});
-  else by_bc(std::integral_constant<int, 19>{});
+  });
 }
 
 template <typename S>
 void Ops<S>::macroscopic(const lbm_lattice* L, void* rho, void* u, bool f64, int rho_mode) {
-  with_model(L, [&](auto kind_c, auto bc_c) {
-    constexpr int KIND = decltype(kind_c)::value;
-    constexpr bool BC = decltype(bc_c)::value;
+  with_read(L, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
     with_field(f64, [&](auto v) {
       using O = decltype(v);
-      hipLaunchKernelGGL((macroscopic_kernel<KIND, S, BC, O>), L->grid, L->block, 0, L->stream,
-                         L->args, L->parity, (long long)L->t, (O*)rho, (O*)u, rho_mode);
+      hipLaunchKernelGGL((macroscopic_kernel<decltype(q_c)::value, S, decltype(odd_c)::value,
+                                             decltype(bc_c)::value, O, decltype(nt_c)::value>),
+                         dim3(L->tiles_all), dim3(256), 0, L->stream, L->args, r, (O*)rho,
+                         (O*)u, rho_mode);
     });
   });
 }
 
 template <typename S>
 void Ops<S>::stats_accumulate(const lbm_lattice* L, double* sums) {
-  with_model(L, [&](auto kind_c, auto bc_c) {
-    constexpr int KIND = decltype(kind_c)::value;
-    constexpr bool BC = decltype(bc_c)::value;
-    hipLaunchKernelGGL((stats_accumulate_kernel<KIND, S, BC>), L->grid, L->block, 0, L->stream,
-                       L->args, L->parity, (long long)L->t, sums);
+  with_read(L, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
+    hipLaunchKernelGGL((stats_accumulate_kernel<decltype(q_c)::value, S, decltype(odd_c)::value,
+                                                decltype(bc_c)::value, decltype(nt_c)::value>),
+                       dim3(L->tiles_all), dim3(256), 0, L->stream, L->args, r, sums);
   });
 }
 
 template <typename S>
-void Ops<S>::reduce_partial(const lbm_lattice* L, dim3 grid, double* partial) {
-  with_model(L, [&](auto kind_c, auto bc_c) {
-    constexpr int KIND = decltype(kind_c)::value;
-    constexpr bool BC = decltype(bc_c)::value;
-    hipLaunchKernelGGL((reduce_partial_kernel<KIND, S, BC>), grid, L->block, 0, L->stream, L->args,
-                       L->parity, (long long)L->t, partial);
+void Ops<S>::reduce_partial(const lbm_lattice* L, unsigned blocks, double* partial) {
+  with_read(L, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
+    hipLaunchKernelGGL((reduce_partial_kernel<decltype(q_c)::value, S, decltype(odd_c)::value,
+                                              decltype(bc_c)::value, decltype(nt_c)::value>),
+                       dim3(blocks), dim3(256), 0, L->stream, L->args, r, partial);
   });
 }
 
