@@ -282,21 +282,17 @@ __device__ __forceinline__ void mrt_vjp(const real (&f)[19], real (&g)[19], cons
     g[i] += db[i] - rb - (real(cx(i)) * jbx + real(cy(i)) * jby + real(cz(i)) * jbz);
 }
 
-// One adjoint step over the rows selected by r. f: natural pre-collision
+// One adjoint step of a node. f: natural pre-collision
 // state at t; ln: adjoint at t+1; l: adjoint at t (all [27][N]); grad:
 // [3][nb][na] inlet-velocity gradient, accumulated by the inlet-plane nodes
 // (each owns its own entry: at most one inlet face).
-template <int KIND, typename real, int BCM, int ROWS>
-__global__ __launch_bounds__(256) void adjoint_kernel(const LatArgs a, const Rows r,
-                                                      const real* __restrict__ f,
-                                                      const real* __restrict__ ln,
-                                                      real* __restrict__ l,
-                                                      double* __restrict__ grad) {
+template <int KIND, typename real, int BCM>
+__device__ __forceinline__ void adjoint_node(const LatArgs& a, const Node& n,
+                                             const real* __restrict__ f,
+                                             const real* __restrict__ ln, real* __restrict__ l,
+                                             double* __restrict__ grad) {
   static_assert(KIND >= 0 && KIND <= 2, "the adjoint covers MRT-LES and FCLB");
   constexpr int Q = Model<KIND>::Q;
-  int x, y, z;
-  if (!row_coords<ROWS>(a, r, x, y, z)) return;
-  const Node n = make_node(a, x, y, z);
   const size_t N = (size_t)a.N;
   // 32-bit byte offsets from per-population bases (see ldo); the wall rows
   // select between a population and its opposite from the lower slab
@@ -381,6 +377,25 @@ __global__ __launch_bounds__(256) void adjoint_kernel(const LatArgs a, const Row
       for (int c = 0; c < 3; ++c) grad[c * nf + idx] += gin[c];
     }
   }
+}
+
+// FLAT or SPLIT (general rules on the listed rows, the wall rules elsewhere).
+template <int KIND, typename real, int BCM, int ROWS>
+__global__ __launch_bounds__(256) void adjoint_kernel(const LatArgs a, const Rows r,
+                                                      const real* __restrict__ f,
+                                                      const real* __restrict__ ln,
+                                                      real* __restrict__ l,
+                                                      double* __restrict__ grad) {
+  int x, y, z;
+  if constexpr (ROWS == ROWS_SPLIT) {
+    if (blockIdx.x < r.list_tiles) {
+      if (list_coords(a, r, x, y, z))
+        adjoint_node<KIND, real, BC_GENERAL>(a, make_node(a, x, y, z), f, ln, l, grad);
+      return;
+    }
+  }
+  if (flat_coords(a, r, ROWS == ROWS_SPLIT ? r.list_tiles : 0, x, y, z))
+    adjoint_node<KIND, real, BCM>(a, make_node(a, x, y, z), f, ln, l, grad);
 }
 
 // Probe objective: J = sum over the box [lo, hi) of |j|^2 / (2 rho), times

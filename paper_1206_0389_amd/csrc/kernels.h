@@ -103,24 +103,25 @@ struct FastDiv {
 
 // Which rows (fixed y, z; all x) a launch covers. FLAT: the nodes n0 .. n1 - 1
 // in memory order less those off y in [y0, y0+ny_in), 256 consecutive ones per
-// workgroup whatever the row length. LIST: the rows lying on a non-periodic y
-// or z face, enumerated as the zb planes first, then the yb rows of every
-// other z; blockIdx.y is the row number. BOX (adjoint): y as for FLAT, z in
-// [z0, z0+nz_in) with blockIdx.z = z - z0, a row per workgroup or several.
+// workgroup whatever the row length. LIST: the nlist nodes of the rows lying on
+// a non-periodic y or z face, enumerated as the zb planes first, then the yb
+// rows of every other z. SPLIT: both, LIST in the first list_tiles workgroups
+// (general rules), FLAT in the others (wall rows).
 //
 // FLAT against BOX for the steps (131 x 97 x 211 MRT FP32, even / odd with
 // walls): 68.9 / 72.5 us against 78.7 / 81.0, as no lane idles at row ends and
 // waves are 256 B runs; 256-node rows: the same. by_xcd: see xcd_tile.
 struct Rows {
-  int y0, ny_in, z0, nz_in;
+  int y0, ny_in;
   int zb_n, zb[2];
   int yb_n, yb[2];
   int zi0;
   uint32_t n0, n1;
+  uint32_t nlist, list_tiles;
   bool by_xcd;
   FastDiv by_nx, by_ny;
 };
-enum { ROWS_BOX = 0, ROWS_LIST = 1, ROWS_FLAT = 2 };
+enum { ROWS_LIST = 1, ROWS_FLAT = 2, ROWS_SPLIT = 3 };
 // Boundary handling of a step kernel: none (all faces periodic), general
 // (any face type, any node), or walls only (rows off every non-periodic z
 // face and off y faces that are not walls; x and y faces WALL or periodic).
@@ -556,15 +557,32 @@ __device__ __forceinline__ real pull_walls(const LatArgs& a, const S* F, const N
     const bool bs = SOLID && ((sb >> I) & 1u) != 0;
     const bool bb = bx || by || bs;
     const uint32_t off = bb ? (I - LO) * slab + (uint32_t)n.self * sz : (IO - LO) * slab + nb;
-    const real v = ldo<real, NT>(F + (size_t)LO * a.N, off);
-    if constexpr ((XB | YB) == 0) {
-      return v;
-    } else {
+    return ldo<real, NT>(F + (size_t)LO * a.N, off);
+  }
+}
+
+// All pulls of a wall-row node: every load, then the wall terms. The barrier
+// keeps the scheduler from mixing the two to save registers, which it does
+// where the general rules share the kernel: a load at a time then (131x97x211
+// MRT FP32: 95 us in place of 63).
+template <int Q, bool NT, bool SOLID, typename real, typename S>
+__device__ __forceinline__ void pull_all_walls(const LatArgs& a, const S* F, const Node& n,
+                                               uint32_t sb, real (&f)[Q]) {
+  static_for<0, Q>([&](auto ic) {
+    constexpr int I = decltype(ic)::value;
+    f[I] = pull_walls<Q, I, real, NT && cx(I) == 0, SOLID>(a, F, n, sb);
+  });
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<0, Q>([&](auto ic) {
+    constexpr int I = decltype(ic)::value;
+    constexpr uint32_t XB = pull_faces(I) & 3u, YB = pull_faces(I) & 12u;
+    if constexpr ((XB | YB) != 0) {
+      const bool bx = (n.atface & XB) != 0, by = (n.atface & YB) != 0;
       const real term =
           wall_row_term<I, real, XB, YB>(a.bc, bx, cx(I) > 0 ? 0 : 1, cy(I) > 0 ? 2 : 3);
-      return (bx || by) ? v + term : v;
+      f[I] = (bx || by) ? f[I] + term : f[I];
     }
-  }
+  });
 }
 
 template <int Q, int I, typename real, bool NT, bool SOLID, typename S>
@@ -607,74 +625,54 @@ __device__ __forceinline__ bool node_coords(const LatArgs& a, int& x, int& y, in
 // The workgroups go round the eight XCDs in launch order; this numbering
 // gives each XCD a contiguous range of 1-D tiles, so that the memory lines two
 // neighbouring tiles share (rows that don't end on one) meet in one L2.
-__device__ __forceinline__ uint32_t xcd_tile(bool by_xcd) {
-  if (!by_xcd) return blockIdx.x;
-  const uint32_t n = gridDim.x, q = n >> 3, r = n & 7u, k = blockIdx.x & 7u;
-  return k * q + min(k, r) + (blockIdx.x >> 3);
+__device__ __forceinline__ uint32_t xcd_tile(bool by_xcd, uint32_t first = 0) {
+  const uint32_t b = blockIdx.x - first;
+  if (!by_xcd) return b;
+  const uint32_t n = gridDim.x - first, q = n >> 3, r = n & 7u, k = b & 7u;
+  return k * q + min(k, r) + (b >> 3);
 }
 
-template <int ROWS>
-__device__ __forceinline__ bool row_coords(const LatArgs& a, const Rows& r, int& x, int& y,
-                                           int& z) {
-  if constexpr (ROWS == ROWS_FLAT) {
-    const uint32_t i = r.n0 + xcd_tile(r.by_xcd) * 256u + threadIdx.x;
-    const uint32_t row = r.by_nx(i), pl = r.by_ny(row);
-    x = (int)(i - row * (uint32_t)a.nx);
-    y = (int)(row - pl * (uint32_t)a.ny);
-    z = (int)pl;
-    return i < r.n1 && y >= r.y0 && y < r.y0 + r.ny_in;
-  }
-  x = blockIdx.x * blockDim.x + threadIdx.x;
-  if constexpr (ROWS == ROWS_BOX) {
-    y = r.y0 + (int)(blockIdx.y * blockDim.y + threadIdx.y);
-    z = r.z0 + (int)blockIdx.z;
-    return x < a.nx && y < r.y0 + r.ny_in;
+// Node of this lane in the FLAT part (workgroups from `first` on) or the
+// LIST; false if there is none.
+__device__ __forceinline__ bool flat_coords(const LatArgs& a, const Rows& r, uint32_t first,
+                                            int& x, int& y, int& z) {
+  const uint32_t i = r.n0 + xcd_tile(r.by_xcd, first) * 256u + threadIdx.x;
+  const uint32_t row = r.by_nx(i), pl = r.by_ny(row);
+  x = (int)(i - row * (uint32_t)a.nx);
+  y = (int)(row - pl * (uint32_t)a.ny);
+  z = (int)pl;
+  return i < r.n1 && y >= r.y0 && y < r.y0 + r.ny_in;
+}
+__device__ __forceinline__ bool list_coords(const LatArgs& a, const Rows& r, int& x, int& y,
+                                            int& z) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  const uint32_t row = r.by_nx(i), planes = (uint32_t)(r.zb_n * a.ny);
+  x = (int)(i - row * (uint32_t)a.nx);
+  if (row < planes) {
+    const uint32_t k = r.by_ny(row);
+    z = k == 0 ? r.zb[0] : r.zb[1];
+    y = (int)(row - k * (uint32_t)a.ny);
   } else {
-    const int row = blockIdx.y;
-    if (row < r.zb_n * a.ny) {
-      z = r.zb[row / a.ny];
-      y = row % a.ny;
-    } else {
-      const int k = row - r.zb_n * a.ny;
-      y = r.yb[k % r.yb_n];
-      z = r.zi0 + k / r.yb_n;
-    }
-    return x < a.nx;
+    const uint32_t k = row - planes;  // yb_n is 2 here
+    y = (k & 1u) ? r.yb[1] : r.yb[0];
+    z = r.zi0 + (int)(k >> 1);
   }
+  return i < r.nlist;
 }
 
-// One collide-and-stream step at time t over the rows selected by r. If rec
+// One collide-and-stream step of a node at time t. If rec
 // is not null, the natural pre-collision state the step collides is also
 // written to rec ([Q][N] in the compute type). The record is a runtime
 // switch, so recording and plain steps run the same code and round alike.
 // EXT: interior solids (wall rows and general kernel) or FREESLIP faces
 // (general kernel) present. NT: streaming hint on the aligned accesses.
-template <int KIND, typename S, bool ODD, int BCM, int ROWS, bool EXT, bool NT>
-__global__ __launch_bounds__(256) void step_kernel(const LatArgs a, const Rows r, long long t,
-                                                   typename Compute<S>::type* rec) {
+template <int KIND, typename S, bool ODD, int BCM, bool EXT, bool NT>
+__device__ __forceinline__ void step_node(const LatArgs& a, const Node& n, long long t,
+                                          typename Compute<S>::type* rec) {
   using M = Model<KIND>;
   using real = typename Compute<S>::type;
   constexpr int Q = M::Q;
   constexpr bool BC = BCM == BC_GENERAL;
-  Node n;
-  if constexpr (ROWS == ROWS_FLAT && !ODD && !EXT) {
-    // even steps touch the node's own slots and, on the outflow plane, the
-    // ghost plane: no coordinates, the place in the plane alone
-    const uint32_t i = r.n0 + xcd_tile(r.by_xcd) * 256u + threadIdx.x;
-    if (i >= r.n1) return;
-    n.self = (int)i;
-    n.atface = 0;
-    n.xo[1] = n.yo[1] = 0;
-    if constexpr (BC) {
-      const uint32_t plane = (uint32_t)a.nx * (uint32_t)a.ny, top = (uint32_t)a.N - plane;
-      n.atface = ((i < plane ? 16u : 0u) | (i >= top ? 32u : 0u)) & a.bc.nonper;
-      n.xo[1] = (int)(i >= top ? i - top : i);
-    }
-  } else {
-    int x, y, z;
-    if (!row_coords<ROWS>(a, r, x, y, z)) return;
-    n = make_node(a, x, y, z);
-  }
   S* __restrict__ F = (S*)a.f;
   const size_t N = (size_t)a.N;
   // interior solids: solid nodes are skipped (the even step runs this only
@@ -706,10 +704,7 @@ __global__ __launch_bounds__(256) void step_kernel(const LatArgs a, const Rows r
     });
   } else {
     if constexpr (BCM == BC_WALLS) {
-      static_for<0, Q>([&](auto ic) {
-        constexpr int I = decltype(ic)::value;
-        f[I] = pull_walls<Q, I, real, NT && cx(I) == 0, EXT>(a, F, n, sb);
-      });
+      pull_all_walls<Q, NT, EXT>(a, F, n, sb, f);
     } else if constexpr (BCM == BC_NONE) {
       static_for<0, Q>([&](auto ic) {
         constexpr int I = decltype(ic)::value;
@@ -796,6 +791,57 @@ __global__ __launch_bounds__(256) void step_kernel(const LatArgs a, const Rows r
       });
     }
   }
+}
+
+// Waves per SIMD that the general rules have to leave to the wall rows of the
+// same launch: FP32 and FP16 steps need three and four (see lds_limit).
+template <typename S, int ROWS>
+constexpr int step_waves() {
+  return ROWS != ROWS_SPLIT ? 1 : (sizeof(S) == 8 ? 2 : (sizeof(S) == 4 ? 3 : 4));
+}
+
+// SPLIT: an odd step with boundaries in one launch. The rows on faces other
+// than walls are few and each takes a long chain of loads and rules; behind
+// the wall rows in a launch of their own they cost 8 us (32x32x64 MRT FP64,
+// wall rows 7 us) to 22 us (96x112x224 MRT FP32 with pressure faces, wall rows
+// 55 us); with the first workgroups of the same launch on them the whole step
+// takes 8.9 and 66 us. Every population has one reader and writer in a step,
+// so their order does not matter.
+template <int KIND, typename S, bool ODD, int BCM, int ROWS, bool EXT, bool NT>
+__global__ __launch_bounds__(256, (step_waves<S, ROWS>())) void step_kernel(
+    const LatArgs a, const Rows r, long long t, typename Compute<S>::type* rec) {
+  Node n;
+  if constexpr (ROWS == ROWS_FLAT && !ODD && !EXT) {
+    // even steps touch the node's own slots and, on the outflow plane, the
+    // ghost plane: no coordinates, the place in the plane alone
+    const uint32_t i = r.n0 + xcd_tile(r.by_xcd) * 256u + threadIdx.x;
+    if (i >= r.n1) return;
+    n.self = (int)i;
+    n.atface = 0;
+    n.xo[1] = n.yo[1] = 0;
+    if constexpr (BCM == BC_GENERAL) {
+      const uint32_t plane = (uint32_t)a.nx * (uint32_t)a.ny, top = (uint32_t)a.N - plane;
+      n.atface = ((i < plane ? 16u : 0u) | (i >= top ? 32u : 0u)) & a.bc.nonper;
+      n.xo[1] = (int)(i >= top ? i - top : i);
+    }
+  } else {
+    int x, y, z;
+    if constexpr (ROWS == ROWS_SPLIT) {
+      if (blockIdx.x < r.list_tiles) {
+        if (!list_coords(a, r, x, y, z)) return;
+        n = make_node(a, x, y, z);
+        step_node<KIND, S, ODD, BC_GENERAL, EXT, false>(a, n, t, rec);
+        return;
+      }
+      if (!flat_coords(a, r, r.list_tiles, x, y, z)) return;
+      n = make_node(a, x, y, z);
+      step_node<KIND, S, ODD, BC_WALLS, false, NT>(a, n, t, rec);
+      return;
+    }
+    if (!(ROWS == ROWS_LIST ? list_coords(a, r, x, y, z) : flat_coords(a, r, 0, x, y, z))) return;
+    n = make_node(a, x, y, z);
+  }
+  step_node<KIND, S, ODD, BCM, EXT, NT>(a, n, t, rec);
 }
 
 // Even step of FP16 storage with two neighbouring nodes per lane (an even
@@ -933,10 +979,7 @@ __device__ __forceinline__ void read_node(const LatArgs& a, const ReadArgs& r, u
       });
     } else if (__builtin_amdgcn_ballot_w64((n.atface & r.general) != 0 ||
                                            r.general == ALL_GENERAL) == 0) {
-      static_for<0, Q>([&](auto ic) {
-        constexpr int I = decltype(ic)::value;
-        f[I] = pull_walls<Q, I, double, false, true>(a, F, n, sb);
-      });
+      pull_all_walls<Q, false, true>(a, F, n, sb, f);
     } else {
       double uin[3] = {0, 0, 0};
       if (n.atface & a.bc.inlet) inlet_velocity(a.bc, n.x, n.y, n.z, r.t - 1, uin);

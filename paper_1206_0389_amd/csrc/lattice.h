@@ -37,8 +37,7 @@ struct lbm_lattice {
   // odd steps with boundaries split into wall rows (x and y faces walls or
   // periodic, see pull_walls) and the rows on the other non-periodic faces
   bool split_odd = false;
-  lbm::Rows rows_all, rows_inner, rows_bnd;
-  dim3 grid_inner, grid_bnd, block_bnd;
+  lbm::Rows rows_all, rows_odd;
   unsigned tiles_all = 0, tiles_inner = 0;  // workgroups of 256 nodes (FLAT)
   bool resident = false;  // populations fit the last-level cache
   // Streaming hint of the steps (see ld): on lattices larger than the

@@ -54,8 +54,6 @@ void plan_rows(lbm_lattice* L) {
   Rows all{};
   all.y0 = 0;
   all.ny_in = ny;
-  all.z0 = 0;
-  all.nz_in = nz;
   all.n0 = 0;
   all.n1 = (uint32_t)L->N;
   all.by_nx.set((uint32_t)nx);
@@ -81,46 +79,42 @@ void plan_rows(lbm_lattice* L) {
   // y faces that are walls stay in the wall rows; other non-periodic y
   // faces go to the row list
   const bool ynp = (np & 12u) != 0 && (L->args.bc.wall & 12u) != 12u;
-  Rows in = all;
+  Rows odd = all;
+  int z0 = 0, nz_in = nz;
   if (ynp) {
-    in.y0 = 1;
-    in.ny_in = ny - 2;
+    odd.y0 = 1;
+    odd.ny_in = ny - 2;
+    odd.yb_n = 2;
+    odd.yb[0] = 0;
+    odd.yb[1] = ny - 1;
   }
   if (znp) {
-    in.z0 = 1;
-    in.nz_in = nz - 2;
+    z0 = 1;
+    nz_in = nz - 2;
+    odd.zb_n = 2;
+    odd.zb[0] = 0;
+    odd.zb[1] = nz - 1;
   }
   const size_t plane = (size_t)nx * ny;
-  in.n0 = (uint32_t)(in.z0 * plane);
-  in.n1 = in.ny_in > 0 && in.nz_in > 0 ? in.n0 + (uint32_t)(in.nz_in * plane) : in.n0;
-  L->tiles_inner = (in.n1 - in.n0 + 255) / 256;
-  L->rows_inner = in;
-  Rows b{};
-  if (znp) {
-    b.zb_n = 2;
-    b.zb[0] = 0;
-    b.zb[1] = nz - 1;
-  }
-  if (ynp) {
-    b.yb_n = 2;
-    b.yb[0] = 0;
-    b.yb[1] = ny - 1;
-  }
-  b.zi0 = znp ? 1 : 0;
-  const long long nrows = (long long)b.zb_n * ny + (long long)b.yb_n * (nz - b.zb_n);
-  L->rows_bnd = b;
+  odd.n0 = (uint32_t)(z0 * plane);
+  odd.n1 = odd.ny_in > 0 && nz_in > 0 ? odd.n0 + (uint32_t)(nz_in * plane) : odd.n0;
+  L->tiles_inner = (odd.n1 - odd.n0 + 255) / 256;
+  odd.zi0 = znp ? 1 : 0;
+  const long long nrows =
+      (long long)odd.zb_n * ny + (long long)odd.yb_n * (nz - odd.zb_n);
   const uint32_t xbits = np & 3u;
   const bool x_ok = (L->args.bc.inlet & 3u) == 0 && (xbits == 0 || (L->args.bc.wall & 3u) == 3u);
   // the wall rows address a population and its opposite from the lower
   // slab with 32-bit offsets: the span of slabs must stay below 4 GiB
   const bool span_ok = slab_span(L->Q) * (double)L->N * (double)L->elem < 4294967296.0;
   L->split_odd = L->has_bc && x_ok && nrows <= 65535 && span_ok;
-  const int bx = L->block.x, by = L->block.y;
-  L->grid_inner = dim3((nx + bx - 1) / bx, in.ny_in > 0 ? (in.ny_in + by - 1) / by : 0,
-                       in.nz_in > 0 ? in.nz_in : 0);
-  const int bbx = nx < 256 ? nx : 256;
-  L->block_bnd = dim3(bbx, 1, 1);
-  L->grid_bnd = dim3((nx + bbx - 1) / bbx, (unsigned)(nrows > 0 ? nrows : 0), 1);
+  if (L->split_odd && nrows > 0) {
+    odd.nlist = (uint32_t)(nrows * nx);
+    // a multiple of eight: the wall rows' tiles behind them stay on the XCDs
+    // of the even step's tiles
+    odd.list_tiles = (odd.nlist + 2047) / 2048 * 8;
+  }
+  L->rows_odd = odd;
 }
 
 // Runs fn(a value of the lattice's storage type).
@@ -730,20 +724,17 @@ int lbm_adjoint_step(lbm_lattice* L, const void* f_t, const void* lambda_next, v
     const R* f = (const R*)f_t;
     const R* ln = (const R*)lambda_next;
     R* l = (R*)lambda;
+    const dim3 block(256), all(L->tiles_all), both(L->rows_odd.list_tiles + L->tiles_inner);
     if (!L->has_bc) {
-      hipLaunchKernelGGL((adjoint_kernel<K, R, BC_NONE, ROWS_BOX>), L->grid, L->block, 0,
-                         L->stream, L->args, L->rows_all, f, ln, l, grad_inlet);
+      hipLaunchKernelGGL((adjoint_kernel<K, R, BC_NONE, ROWS_FLAT>), all, block, 0, L->stream,
+                         L->args, L->rows_all, f, ln, l, grad_inlet);
     } else if (!split) {
-      hipLaunchKernelGGL((adjoint_kernel<K, R, BC_GENERAL, ROWS_BOX>), L->grid, L->block, 0,
-                         L->stream, L->args, L->rows_all, f, ln, l, grad_inlet);
+      hipLaunchKernelGGL((adjoint_kernel<K, R, BC_GENERAL, ROWS_FLAT>), all, block, 0, L->stream,
+                         L->args, L->rows_all, f, ln, l, grad_inlet);
     } else {
-      if (L->grid_inner.y > 0 && L->grid_inner.z > 0)
-        hipLaunchKernelGGL((adjoint_kernel<K, R, BC_WALLS, ROWS_BOX>), L->grid_inner, L->block,
-                           0, L->stream, L->args, L->rows_inner, f, ln, l, grad_inlet);
-      if (L->grid_bnd.y > 0)
-        hipLaunchKernelGGL((adjoint_kernel<K, R, BC_GENERAL, ROWS_LIST>), L->grid_bnd,
-                           L->block_bnd, 0, L->stream, L->args, L->rows_bnd, f, ln, l,
-                           grad_inlet);
+      hipLaunchKernelGGL((adjoint_kernel<K, R, BC_WALLS, ROWS_SPLIT>),
+                         both, block, 0, L->stream,
+                         L->args, L->rows_odd, f, ln, l, grad_inlet);
     }
   };
   auto by_type = [&](auto kind_c) {
