@@ -733,8 +733,16 @@ void inject(lbm_refined* R, int l, hipStream_t stream) {
                      rescale_args(R, l + 1));
 }
 
-// One step of level l on stream st: the solid pre-pass, then the tile
-// classes.
+// LDS requested by a level step beyond the last-level cache, to leave room on
+// each CU for the interface kernels of the other stream (four workgroups of
+// the step, as for lds_limit of the uniform lattice): 96x96x192 jet with
+// 128x128x192 fine nodes, FCLB FP32, four steps and fields: 2735 us without,
+// 2595 with four, 2604 with three workgroups per CU.
+unsigned level_lds(const HostLevel& V, int Q, size_t elem) {
+  return elem >= 4 && (double)V.Nbox * Q * (double)elem > 256.0 * 1048576.0 ? 40u * 1024u : 0u;
+}
+
+// One step of level l on stream st: the solid pre-pass, then the tiles.
 template <int KIND, typename S>
 void level_step(lbm_refined* R, int l, long long t, hipStream_t st) {
   HostLevel& V = R->lev[l];
@@ -748,25 +756,12 @@ void level_step(lbm_refined* R, int l, long long t, hipStream_t st) {
                        (const uint32_t*)(R->base + V.off_pre_dirs),
                        (const float*)(R->base + V.off_pre_q), (long long)V.pre_nodes.size());
   }
-  const int* tiles = (const int*)(R->base + V.off_tiles);
-  size_t start = 0;
-  for (int k = 0; k < 3; ++k) {
-    const size_t n = V.nt[k];
-    const int* tl = tiles + 3 * start;
-    start += n;
-    if (n == 0) continue;
-    const dim3 grid((unsigned)n), block(256);
-    static const char* const names[3] = {"level_step_kernel (general tiles)",
-                                         "level_step_kernel (wall tiles)",
-                                         "level_step_kernel (plain tiles)"};
-    TraceScope ts(R->tracer.get(), st, names[k], l);
-    if (k == 0)
-      hipLaunchKernelGGL((level_step_kernel<KIND, S, TILE_GENERAL>), grid, block, 0, st, D, tl, t);
-    else if (k == 1)
-      hipLaunchKernelGGL((level_step_kernel<KIND, S, TILE_WALLS>), grid, block, 0, st, D, tl, t);
-    else
-      hipLaunchKernelGGL((level_step_kernel<KIND, S, TILE_PLAIN>), grid, block, 0, st, D, tl, t);
-  }
+  const size_t n = V.nt[0] + V.nt[1] + V.nt[2];
+  if (n == 0) return;
+  TraceScope ts(R->tracer.get(), st, "level_step_kernel (all tiles)", l);
+  hipLaunchKernelGGL((level_step_kernel<KIND, S>), dim3((unsigned)n), dim3(256),
+                     level_lds(V, R->Q, sizeof(S)), st, D,
+                     (const int*)(R->base + V.off_tiles), (unsigned)V.nt[0], (unsigned)V.nt[1], t);
 }
 
 // After a step of level V: the array written becomes the one read, the one

@@ -294,8 +294,8 @@ __device__ __forceinline__ bool in_box(const Lev& L, const int (&g)[3], int& sel
 
 // Pull of population I at a node whose sources lie in the box without
 // wrapping except across x or y WALL faces (wall tiles): across such a face
-// the node's own slot opp(I) plus the wall term 6 w_I e_I.u_w (the x face
-// first where a node lies on both); both candidate slots are offsets from
+// the node's own slot opp(I), to which the caller adds the wall term 6 w_I
+// e_I.u_w (the x face first where a node lies on both); both candidate slots are offsets from
 // the lower of the two population slabs, so one scalar-base load serves.
 template <int Q, int I, typename real, typename S>
 __device__ __forceinline__ real walls_pull(const Lev& L, const S* A, int self, int src,
@@ -312,84 +312,106 @@ __device__ __forceinline__ real walls_pull(const Lev& L, const S* A, int self, i
     const bool bb = bx || by;
     const uint32_t off = bb ? (uint32_t)(IO - LO) * slab + (uint32_t)self * sz
                             : (uint32_t)(I - LO) * slab + (uint32_t)src * sz;
-    const real v = ldo<real, cx(I) == 0>(A + (size_t)LO * L.Nbox, off);
-    const real term =
-        wall_row_term<I, real, XB, YB>(L.bc, bx, cx(I) > 0 ? 0 : 1, cy(I) > 0 ? 2 : 3);
-    return bb ? v + term : v;
+    return ldo<real, cx(I) == 0>(A + (size_t)LO * L.Nbox, off);
   }
 }
 
 // ------------------------------------------------------------- level step
 enum { TILE_PLAIN = 0, TILE_WALLS = 1, TILE_GENERAL = 2 };
 
-// One pull-and-collide step of level L at its step index t over a tile
-// list. KINDT: TILE_PLAIN (every source of the tile's active nodes lies in
-// the box without wrapping, no node on a domain face), TILE_WALLS (as plain
-// but with x or y WALL faces, the wall-row rule) or TILE_GENERAL (periodic
-// wrap and every face rule).
+// One pull-and-collide step of a node. KINDT: TILE_PLAIN (every source of the
+// tile's active nodes lies in the box without wrapping, no node on a domain
+// face), TILE_WALLS (as plain but with x or y WALL faces, the wall-row rule)
+// or TILE_GENERAL (periodic wrap and every face rule). The barriers keep the
+// loads together, see pull_all_walls.
 template <int KIND, typename S, int KINDT>
-__global__ __launch_bounds__(256) void level_step_kernel(const Lev L, const int* tiles,
-                                                         long long t) {
+__device__ __forceinline__ void level_node(const Lev& L, const int (&g)[3], int self,
+                                           long long t) {
   using M = Model<KIND>;
   using real = typename Compute<S>::type;
   constexpr int Q = M::Q;
-  int g[3], self = 0;
-  tile_node(L, tiles, g);
-  bool active = in_box(L, g, self);
-  if (active) {
-    const uint8_t ty = L.type[self];
-    active = ty == RT_FLUID || ty == RT_BAND;
-  }
-  if (!active) return;
   const S* A = (const S*)L.a;
   S* B = (S*)L.b;
   const size_t N = (size_t)L.Nbox;
   real f[Q];
-  if (active) {
-    if constexpr (KINDT == TILE_GENERAL) {
-      const BoxNode n = make_box_node(L, g);
-      static_for<0, Q>([&](auto ic) {
-        constexpr int I = decltype(ic)::value;
-        f[I] = ld<real>(gen_pull_addr<Q, I, S>(L, A, n));
-      });
-      if (n.atface) {
-        double uin[3] = {0, 0, 0};
-        if (n.atface & L.bc.inlet) inlet_velocity(L.bc, g[0], g[1], g[2], t, uin);
-        const real up[3] = {real(uin[0]), real(uin[1]), real(uin[2])};
-        static_for<0, Q>([&](auto ic) {
-          constexpr int I = decltype(ic)::value;
-          f[I] += pull_term<Q, I, real>(L.bc, n.atface, up);
-        });
-        if (n.atface & L.bc.pressure) gen_pressure<KIND, real, S>(L, A, n, f);
-      }
-    } else if constexpr (KINDT == TILE_WALLS) {
-      const int sy = L.M[0], sz = L.M[0] * L.M[1];
-      uint32_t m = 0;
-      m |= g[0] == 0 ? 1u : 0u;
-      m |= g[0] == L.n[0] - 1 ? 2u : 0u;
-      m |= g[1] == 0 ? 4u : 0u;
-      m |= g[1] == L.n[1] - 1 ? 8u : 0u;
-      m &= L.bc.wall;
-      static_for<0, Q>([&](auto ic) {
-        constexpr int I = decltype(ic)::value;
-        const int src = self - cx(I) - cy(I) * sy - cz(I) * sz;
-        f[I] = walls_pull<Q, I, real, S>(L, A, self, src, m);
-      });
-    } else {
-      const int sy = L.M[0], sz = L.M[0] * L.M[1];
-      static_for<0, Q>([&](auto ic) {
-        constexpr int I = decltype(ic)::value;
-        const int src = self - cx(I) - cy(I) * sy - cz(I) * sz;
-        f[I] = ldo<real, cx(I) == 0>(A + (size_t)I * N, (uint32_t)src * (uint32_t)sizeof(S));
-      });
-    }
-    M::collide(f, L);
-    const uint32_t so = (uint32_t)self * (uint32_t)sizeof(S);
+  if constexpr (KINDT == TILE_GENERAL) {
+    const BoxNode n = make_box_node(L, g);
     static_for<0, Q>([&](auto ic) {
       constexpr int I = decltype(ic)::value;
-      sto<true>(B + (size_t)I * N, so, f[I]);
+      f[I] = ld<real>(gen_pull_addr<Q, I, S>(L, A, n));
     });
+    if (n.atface) {
+      double uin[3] = {0, 0, 0};
+      if (n.atface & L.bc.inlet) inlet_velocity(L.bc, g[0], g[1], g[2], t, uin);
+      const real up[3] = {real(uin[0]), real(uin[1]), real(uin[2])};
+      static_for<0, Q>([&](auto ic) {
+        constexpr int I = decltype(ic)::value;
+        f[I] += pull_term<Q, I, real>(L.bc, n.atface, up);
+      });
+      if (n.atface & L.bc.pressure) gen_pressure<KIND, real, S>(L, A, n, f);
+    }
+  } else if constexpr (KINDT == TILE_WALLS) {
+    const int sy = L.M[0], sz = L.M[0] * L.M[1];
+    uint32_t m = 0;
+    m |= g[0] == 0 ? 1u : 0u;
+    m |= g[0] == L.n[0] - 1 ? 2u : 0u;
+    m |= g[1] == 0 ? 4u : 0u;
+    m |= g[1] == L.n[1] - 1 ? 8u : 0u;
+    m &= L.bc.wall;
+    static_for<0, Q>([&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      const int src = self - cx(I) - cy(I) * sy - cz(I) * sz;
+      f[I] = walls_pull<Q, I, real, S>(L, A, self, src, m);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, Q>([&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      constexpr uint32_t XB = pull_faces(I) & 3u, YB = pull_faces(I) & 12u;
+      if constexpr ((XB | YB) != 0) {
+        const bool bx = (m & XB) != 0, by = (m & YB) != 0;
+        const real term =
+            wall_row_term<I, real, XB, YB>(L.bc, bx, cx(I) > 0 ? 0 : 1, cy(I) > 0 ? 2 : 3);
+        f[I] = (bx || by) ? f[I] + term : f[I];
+      }
+    });
+  } else {
+    const int sy = L.M[0], sz = L.M[0] * L.M[1];
+    static_for<0, Q>([&](auto ic) {
+      constexpr int I = decltype(ic)::value;
+      const int src = self - cx(I) - cy(I) * sy - cz(I) * sz;
+      f[I] = ldo<real, cx(I) == 0>(A + (size_t)I * N, (uint32_t)src * (uint32_t)sizeof(S));
+    });
+    __builtin_amdgcn_sched_barrier(0);
   }
+  M::collide(f, L);
+  const uint32_t so = (uint32_t)self * (uint32_t)sizeof(S);
+  static_for<0, Q>([&](auto ic) {
+    constexpr int I = decltype(ic)::value;
+    sto<true>(B + (size_t)I * N, so, f[I]);
+  });
+}
+
+// One step of level L at its step index t over its tile list: first the
+// ngeneral general tiles, then the nwalls wall tiles, then the plain ones.
+// One launch for the three classes: the general tiles are few and take a long
+// chain of loads and rules each, alone 58 us on level 0 and 17 us on level 1
+// of a 96x96x192 jet with 128x128x192 fine nodes (FCLB FP32), before the
+// others could start.
+template <int KIND, typename S>
+__global__ __launch_bounds__(256) void level_step_kernel(const Lev L, const int* tiles,
+                                                         unsigned ngeneral, unsigned nwalls,
+                                                         long long t) {
+  int g[3], self = 0;
+  tile_node(L, tiles, g);
+  if (!in_box(L, g, self)) return;
+  const uint8_t ty = L.type[self];
+  if (ty != RT_FLUID && ty != RT_BAND) return;
+  if (blockIdx.x < ngeneral)
+    level_node<KIND, S, TILE_GENERAL>(L, g, self, t);
+  else if (blockIdx.x < ngeneral + nwalls)
+    level_node<KIND, S, TILE_WALLS>(L, g, self, t);
+  else
+    level_node<KIND, S, TILE_PLAIN>(L, g, self, t);
 }
 
 // Covered parent nodes := f_eq + rescaled-back (m - f_eq), m = the mean of
