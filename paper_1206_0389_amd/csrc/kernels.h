@@ -803,9 +803,9 @@ constexpr int step_waves() {
 // SPLIT: an odd step with boundaries in one launch. The rows on faces other
 // than walls are few and each takes a long chain of loads and rules; behind
 // the wall rows in a launch of their own they cost 8 us (32x32x64 MRT FP64,
-// wall rows 7 us) to 22 us (96x112x224 MRT FP32 with pressure faces, wall rows
-// 55 us); with the first workgroups of the same launch on them the whole step
-// takes 8.9 and 66 us. Every population has one reader and writer in a step,
+// wall rows 7 us) to 11 us (131x97x211 MRT FP32, wall rows 63 us); with the
+// first workgroups of the same launch on them the whole step takes 8.9 and 63
+// us. Every population has one reader and writer in a step,
 // so their order does not matter.
 template <int KIND, typename S, bool ODD, int BCM, int ROWS, bool EXT, bool NT>
 __global__ __launch_bounds__(256, (step_waves<S, ROWS>())) void step_kernel(

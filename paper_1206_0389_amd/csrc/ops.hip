@@ -61,32 +61,25 @@ void step_model_ext(const lbm_lattice* L, bool odd, long long t, void* rec) {
     launch_step<KIND, S, true, BC_GENERAL, ROWS_FLAT, EXT, false>(L, grid, block, L->rows_all, t,
                                                                   rec);
   } else {
-    // one launch, except with solids, whose wall rows need the registers that
-    // the general rules would take, and in FP16 (256x256x512 FCLB: 805 us in
-    // one, 763 + 16 us apart)
+    // One launch, except in FP16 (256x256x512 FCLB 805 us, apart 763 + 16) and
+    // with the rules of EXT, whose registers spill beside the wall rows: they
+    // win on a large lattice (96x112x224 MRT FP32 tank, ten steps 722 us
+    // against 778) but cost on small ones (94x73x33, ten steps: FCLB 353 us
+    // against 192, MRT 200 against 142).
     const Rows& r = L->rows_odd;
     const dim3 inner(L->tiles_inner), list(r.list_tiles), both(r.list_tiles + L->tiles_inner);
-    if constexpr (!std::is_same_v<S, _Float16>) {
-      if (!L->solids) {
-        launch_step<KIND, S, true, BC_WALLS, ROWS_SPLIT, EXT, NT>(L, both, block, r, t, rec);
-        return;
-      }
-    }
-    if (inner.x > 0) {
-      bool done = false;
-      if constexpr (EXT) {
-        if (L->solids) {
-          launch_step<KIND, S, true, BC_WALLS, ROWS_FLAT, true, NT>(L, inner, block, r, t, rec);
-          done = true;
-        }
-      }
-      if constexpr (std::is_same_v<S, _Float16>) {
-        if (!done)
+    if constexpr (!EXT && !std::is_same_v<S, _Float16>) {
+      launch_step<KIND, S, true, BC_WALLS, ROWS_SPLIT, false, NT>(L, both, block, r, t, rec);
+    } else {
+      if (inner.x > 0) {
+        if (EXT && L->solids)
+          launch_step<KIND, S, true, BC_WALLS, ROWS_FLAT, EXT, NT>(L, inner, block, r, t, rec);
+        else
           launch_step<KIND, S, true, BC_WALLS, ROWS_FLAT, false, NT>(L, inner, block, r, t, rec);
       }
+      if (list.x > 0)
+        launch_step<KIND, S, true, BC_GENERAL, ROWS_LIST, EXT, false>(L, list, block, r, t, rec);
     }
-    if (list.x > 0)
-      launch_step<KIND, S, true, BC_GENERAL, ROWS_LIST, EXT, false>(L, list, block, r, t, rec);
   }
 }
 
