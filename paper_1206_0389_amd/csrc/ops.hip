@@ -64,7 +64,7 @@ void step_model_ext(const lbm_lattice* L, bool odd, long long t, void* rec) {
     // One launch, except in FP16 (256x256x512 FCLB 805 us, apart 763 + 16) and
     // with the rules of EXT, whose registers spill beside the wall rows: they
     // win on a large lattice (96x112x224 MRT FP32 tank, ten steps 722 us
-    // against 778) but cost on small ones (94x73x33, ten steps: FCLB 353 us
+    // against 741) but cost on small ones (94x73x33, ten steps: FCLB 353 us
     // against 192, MRT 200 against 142).
     const Rows& r = L->rows_odd;
     const dim3 inner(L->tiles_inner), list(r.list_tiles), both(r.list_tiles + L->tiles_inner);
