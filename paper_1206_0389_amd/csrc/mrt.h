@@ -167,9 +167,18 @@ struct MrtParams {
 //               every b at s7.
 //   d'Humieres: eps = 21 (b sum) - 16 (trace) and the deviator of pi, 3 b' -
 //               2 n' with b'_yz paired to n'_xx, mix orders 2 and 4.
-// 283 VALU instructions per node in the FP32 even step, 558 with the two
-// unrolled 19 x 19 products; the error against 64-bit arithmetic is smaller
-// for Table 1 (1e-7 to 7.6e-8 of the velocity after 10 steps).
+// Small moments are formed from differences in which what the populations
+// have in common (drho / 3, j_a / 3) has dropped out, never by subtracting
+// it from sums that carry it: the deviators from differences of two axes,
+// the trace from (b sum) - f_0. The shear rate near 2 (tau0 < 1) is used as
+// 2 - gap: rounding 1/tau itself shifts the viscosity by up to 6e-8 tau /
+// (tau - 1/2), which adds up over the steps. FP32 against 64 bits, velocity,
+// 24^3 periodic waves at nu 1e-3, this form / the unrolled 19 x 19 products:
+// Table 1 3.3e-8 / 7.5e-8 after 6 steps, 2.7e-7 / 9.2e-7 after 300,
+// d'Humieres 4.5e-8 / 6.9e-8 and 3.3e-7 / 1.2e-6.
+// 289 VALU instructions per node in the FP32 even step, 558 with the
+// products; the steps, bound by memory, take the same time as before the
+// differences (131x97x211 jet, ten steps and populations: 687 us).
 template <typename real, int BASIS>
 __device__ __forceinline__ void mrt_collide(real (&f)[19], const MrtParams& p) {
   // the four diagonals of the xy, xz and yz planes: ++, --, +-, -+
@@ -190,74 +199,77 @@ __device__ __forceinline__ void mrt_collide(real (&f)[19], const MrtParams& p) {
   }
   const real sx = f[1] + f[2], sy = f[3] + f[4], sz = f[5] + f[6];
   const real ax = A1[0] + A1[1], ay = A2[0] + A1[2], az = A2[1] + A2[2];
-  const real jx = (f[1] - f[2]) + ax, jy = (f[3] - f[4]) + ay, jz = (f[5] - f[6]) + az;
+  const real gx = f[1] - f[2], gy = f[3] - f[4], gz = f[5] - f[6];
+  const real jx = gx + ax, jy = gy + ay, jz = gz + az;
   const real drho = f[0] + ((sx + sy + sz) + (B[0] + B[1] + B[2]));
   const real third = real(1.0 / 3.0), sixth = real(1.0 / 6.0), two3 = real(2.0 / 3.0);
   const real xx = jx * jx, yy = jy * jy, zz = jz * jz;
-  const real r3 = third * drho, r9 = third * r3;
-  const real nxx = (sx + (B[0] + B[1])) - (r3 + xx);
-  const real nyy = (sy + (B[0] + B[2])) - (r3 + yy);
-  const real nzz = (sz + (B[1] + B[2])) - (r3 + zz);
+  const real r9 = real(1.0 / 9.0) * drho;
+  const real d1 = (sx - sy) + (B[1] - B[2]) - (xx - yy);
+  const real d2 = (sx - sz) + (B[0] - B[2]) - (xx - zz);
+  const real dxx = third * (d1 + d2), dyy = third * (d2 - real(2) * d1),
+             dzz = third * (d1 - real(2) * d2);
+  const real tr = ((B[0] + B[1] + B[2]) - f[0]) - (xx + yy + zz), t3 = third * tr;
   const real nxy = X[0] - jx * jy, nxz = X[1] - jx * jz, nyz = X[2] - jy * jz;
   // the strain-dependent relaxation time, Eqs. (19)-(21)
-  const real pi2 = nxx * nxx + nyy * nyy + nzz * nzz +
+  const real pi2 = dxx * dxx + dyy * dyy + dzz * dzz + tr * t3 +
                    real(2) * (nxy * nxy + nxz * nxz + nyz * nyz);
   const real Qs = sqrt(real(2) * pi2);
-  const real tau0 = real(p.tau0);
-  const real tau = real(0.5) * (tau0 + sqrt(tau0 * tau0 + real(p.cs18) * Qs));
-  const real ss = real(1) / tau;
+  const real tau0 = real(p.tau0), les = real(p.cs18) * Qs;
+  const real i2t = real(1) / (tau0 + sqrt(tau0 * tau0 + les));  // 1 / (2 tau)
+  // 1 / tau = top - gap, gap = (2 tau - 1) / tau, 2 tau - 1 = 2 tau0 - 1 +
+  // les / (2 tau) for rates near 2, else the rate itself
+  const bool low = p.tau0 < 1.0;
+  const real top = low ? real(2) : real(0);
+  const real gap = real(2) * i2t * (low ? real(2.0 * p.tau0 - 1.0) + les * i2t : real(-1));
   const real bxy = B[0] - (r9 + third * (xx + yy) - sixth * zz);
   const real bxz = B[1] - (r9 + third * (xx + zz) - sixth * yy);
   const real byz = B[2] - (r9 + third * (yy + zz) - sixth * xx);
   // changes c of the raw moments
   const real s_tr = real(p.rates[0]);
-  const real tr = nxx + nyy + nzz, t3 = third * tr, ct = s_tr * t3;
-  const real dxx = nxx - t3, dyy = nyy - t3, dzz = nzz - t3;
-  const real cxx = ss * dxx + ct, cyy = ss * dyy + ct, czz = ss * dzz + ct;
-  const real q4 = real(0.25), s4 = q4 * ss;
+  const real ct = s_tr * t3;
+  const real cxx = top * dxx + (ct - gap * dxx), cyy = top * dyy + (ct - gap * dyy),
+             czz = top * dzz + (ct - gap * dzz);
+  const real q4 = real(0.25), t4 = q4 * top, g4 = q4 * gap;
   const real hs = real(0.5) * real(BASIS == 0 ? p.rates[1] : p.rates[2]);
   const real ha = real(0.5) * real(BASIS == 0 ? p.rates[2] : p.rates[4]);
-  real c1[3], c2[3];  // c of a, per plane (first and second axis odd)
-  {
-    // (the equilibrium's j_a/3 drops out of the differences)
-    const real x0 = hs * (ax - two3 * jx), x1 = ha * (A1[0] - A1[1]);
-    const real y0 = hs * (ay - two3 * jy), y1 = ha * (A2[0] - A1[2]);
-    const real z0 = hs * (az - two3 * jz), z1 = ha * (A2[1] - A2[2]);
-    c1[0] = x0 + x1;
-    c1[1] = x0 - x1;
-    c2[0] = y0 + y1;
-    c1[2] = y0 - y1;
-    c2[1] = z0 + z1;
-    c2[2] = z0 - z1;
-  }
-  real cb[3];
+  // c of a, per plane (first and second axis odd); the equilibrium's j_a/3
+  // drops out of the differences, and a_ab + a_ac - 2 j_a / 3 is a third of
+  // a_ab + a_ac - 2 g_a, g_a the axis populations' difference
+  const real x0 = hs * (third * (ax - real(2) * gx)), x1 = ha * (A1[0] - A1[1]);
+  const real y0 = hs * (third * (ay - real(2) * gy)), y1 = ha * (A2[0] - A1[2]);
+  const real z0 = hs * (third * (az - real(2) * gz)), z1 = ha * (A2[1] - A2[2]);
+  const real c1[3] = {x0 + x1, x0 - x1, y0 - y1}, c2[3] = {y0 + y1, z0 + z1, z0 - z1};
+  real cb[3], cbs;  // c of b and their sum
   if constexpr (BASIS == 0) {
     const real s7 = real(p.rates[3]);
     cb[0] = s7 * bxy;
     cb[1] = s7 * bxz;
     cb[2] = s7 * byz;
+    cbs = cb[0] + cb[1] + cb[2];
   } else {
     const real s_eps = real(p.rates[1]), s_pi = real(p.rates[3]);
-    const real base = third * ((s_eps - s_pi) * (bxy + bxz + byz) +
-                               real(16.0 / 21.0) * (s_tr - s_eps) * tr);
-    const real mix = two3 * (s_pi - ss);
-    cb[0] = base + s_pi * bxy + mix * dzz;
-    cb[1] = base + s_pi * bxz + mix * dyy;
-    cb[2] = base + s_pi * byz + mix * dxx;
+    cbs = s_eps * (bxy + bxz + byz) + real(16.0 / 21.0) * (s_tr - s_eps) * tr;
+    const real mix = two3 * ((s_pi - top) + gap), base = third * cbs;
+    const real g1 = (B[0] - B[1]) - real(0.5) * (yy - zz);
+    const real g2 = (B[0] - B[2]) - real(0.5) * (xx - zz);
+    cb[0] = base + s_pi * (third * (g1 + g2)) + mix * dzz;
+    cb[1] = base + s_pi * (third * (g2 - real(2) * g1)) + mix * dyy;
+    cb[2] = base + s_pi * (third * (g1 - real(2) * g2)) + mix * dxx;
   }
   // D3Q19 inverse of the changes
-  f[0] += (cxx + cyy + czz) - (cb[0] + cb[1] + cb[2]);
+  f[0] += real(3) * ct - cbs;
   const real h = real(0.5);
-  const real ex = h * (cxx - cb[0] - cb[1]), ox = h * (c1[0] + c1[1]);
-  const real ey = h * (cyy - cb[0] - cb[2]), oy = h * (c2[0] + c1[2]);
-  const real ez = h * (czz - cb[1] - cb[2]), oz = h * (c2[1] + c2[2]);
-  f[1] -= ex - ox;
-  f[2] -= ex + ox;
-  f[3] -= ey - oy;
-  f[4] -= ey + oy;
-  f[5] -= ez - oz;
-  f[6] -= ez + oz;
-  const real x[3] = {s4 * nxy, s4 * nxz, s4 * nyz};
+  const real ex = h * (cxx - cb[0] - cb[1]);
+  const real ey = h * (cyy - cb[0] - cb[2]);
+  const real ez = h * (czz - cb[1] - cb[2]);
+  f[1] -= ex - x0;
+  f[2] -= ex + x0;
+  f[3] -= ey - y0;
+  f[4] -= ey + y0;
+  f[5] -= ez - z0;
+  f[6] -= ez + z0;
+  const real x[3] = {t4 * nxy - g4 * nxy, t4 * nxz - g4 * nxz, t4 * nyz - g4 * nyz};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const real e = q4 * cb[k] + x[k], o = q4 * cb[k] - x[k];
