@@ -733,13 +733,17 @@ void inject(lbm_refined* R, int l, hipStream_t stream) {
                      rescale_args(R, l + 1));
 }
 
-// LDS requested by a level step beyond the last-level cache, to leave room on
-// each CU for the interface kernels of the other stream (four workgroups of
-// the step, as for lds_limit of the uniform lattice): 96x96x192 jet with
-// 128x128x192 fine nodes, FCLB FP32, four steps and fields: 2735 us without,
-// 2595 with four, 2604 with three workgroups per CU.
+// LDS requested by the D3Q19 FP32 level steps beyond the last-level cache, to
+// leave room on each CU for the interface kernels of the other stream (four
+// workgroups of the step, as for lds_limit of the uniform lattice). Four
+// steps of the jet on two levels with 16^3 blocks, us without / with, by the
+// cells of level 0 across: MRT FP32 96 1700 / 1679, 112 2692 / 2622, 128 3763
+// / 3663. The other steps' registers leave no more than four on a CU as it is,
+// and they gain nothing: FCLB FP32 2346 / 2342, 3808 / 3797, 5259 / 5273; 96
+// and 112 in FP64, MRT 2640 / 2648, 4310 / 4330, FCLB 3772 / 3780, 6138 / 6204.
 unsigned level_lds(const HostLevel& V, int Q, size_t elem) {
-  return elem >= 4 && (double)V.Nbox * Q * (double)elem > 256.0 * 1048576.0 ? 40u * 1024u : 0u;
+  return Q == 19 && elem == 4 && (double)V.Nbox * Q * (double)elem > 256.0 * 1048576.0
+             ? 40u * 1024u : 0u;
 }
 
 // One step of level l on stream st: the solid pre-pass, then the tiles.
