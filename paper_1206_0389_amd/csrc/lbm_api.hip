@@ -732,6 +732,17 @@ int lbm_adjoint_step(lbm_lattice* L, const void* f_t, const void* lambda_next, v
       hipLaunchKernelGGL((adjoint_kernel<K, R, BC_GENERAL, ROWS_FLAT>), all, block, 0, L->stream,
                          L->args, L->rows_all, f, ln, l, grad_inlet);
     } else {
+      if constexpr (std::is_same_v<R, double>) {
+        // Without listed rows FP64 leaves the general rules' registers out (64^3
+        // channel FCLB 34.9 to 33.0 us, MRT 22.4 to 21.3, 94x73x33 33.8 to 31.0,
+        // 21.8 to 20.6; from 128^3 on within 2 %). FP32 has room for them and is
+        // slower apart (131x97x211 MRT 134 and 145 us).
+        if (L->rows_odd.list_tiles == 0) {
+          hipLaunchKernelGGL((adjoint_kernel<K, R, BC_WALLS, ROWS_FLAT>), dim3(L->tiles_inner),
+                             block, 0, L->stream, L->args, L->rows_odd, f, ln, l, grad_inlet);
+          return;
+        }
+      }
       hipLaunchKernelGGL((adjoint_kernel<K, R, BC_WALLS, ROWS_SPLIT>),
                          both, block, 0, L->stream,
                          L->args, L->rows_odd, f, ln, l, grad_inlet);
