@@ -63,9 +63,18 @@ void step_model_ext(const lbm_lattice* L, bool odd, long long t, void* rec) {
   } else {
     // One launch, except in FP16 (256x256x512 FCLB 805 us, apart 763 + 16) and
     // with the rules of EXT, whose registers spill beside the wall rows: they
-    // win on a large lattice (96x112x224 MRT FP32 tank, ten steps 722 us
-    // against 741) but cost on small ones (94x73x33, ten steps: FCLB 353 us
-    // against 192, MRT 200 against 142).
+    // win on a large lattice (96x112x224 MRT FP32 tank, ten steps 722 us against
+    // 741) but cost on small ones (94x73x33, ten steps: FCLB 353 us against 192,
+    // MRT 200 against 142). Without EXT one launch is the faster at every size
+    // where rows are listed, though the wall rows keep three waves in FP32 and
+    // two in FP64 beside the general rules and FCLB and CLB FP32 spill there too
+    // (jet, us per step in one / two launches: 16^3 FCLB FP32 7.7 / 9.7, MRT
+    // FP64 5.7 / 9.2, 64^3 FCLB FP32 13.7 / 14.0, FP64 20.7 / 25.6, MRT FP32 7.9
+    // / 10.6, 131x97x211 110 / 115, 243 / 253, 62 / 67).
+    // Where no row is listed the rules cost nothing to speak of (channel, with /
+    // without them: 64^3 FCLB FP32 8.8 / 8.4, FP64 19.4 / 19.5, MRT FP32 8.2 /
+    // 7.9; 100x75x110 29.1 / 28.9, 54.5 / 54.5, 21.3 / 21.0; 192x160x200 224 /
+    // 225, 462 / 462, 150 / 151).
     const Rows& r = L->rows_odd;
     const dim3 inner(L->tiles_inner), list(r.list_tiles), both(r.list_tiles + L->tiles_inner);
     if constexpr (!EXT && !std::is_same_v<S, _Float16>) {
