@@ -73,6 +73,7 @@ void plan_rows(lbm_lattice* L) {
   all.by_xcd = L->resident;
   L->nt_even = !L->resident && (L->N * L->elem) % 128 == 0;
   L->nt_odd = !L->resident && ((size_t)nx * L->elem) % 128 == 0;
+  L->nt_read = bytes > 4.0 / 3.0 * 256.0 * 1048576.0;
   L->tiles_all = (unsigned)((L->N + 255) / 256);
   L->rows_all = all;
   const bool znp = (np & 48u) != 0;

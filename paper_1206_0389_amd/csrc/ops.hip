@@ -162,11 +162,15 @@ void with_field(bool f64, Fn&& fn) {
 
 // Runs fn(Q, odd parity, boundaries, streaming hint, ReadArgs) for a readout.
 // The hint at even parity, whose accesses run from end to end, on lattices
-// that the last-level cache does not hold (as for the steps). Workgroups per
-// CU are not limited here: fewer cost (256x256x512 FCLB FP16, density and
-// velocity: 382 us; 455 us with three).
+// larger than the last-level cache: by `hint`, over a third larger for what
+// reads the populations and little else. Up to there enough of them is still
+// cached (density and velocity after two steps with / without it, us: 270 MiB
+// MRT FP32 161x153x151 67.5 / 57.9, 304 MiB MRT FP64 128^3 68 / 55; 383 MiB
+// FCLB FP32 161x153x151 71 / 118). Workgroups per CU are not limited here: fewer
+// cost (256x256x512 FCLB FP16, density and velocity: 382 us; 455 us with
+// three).
 template <typename Fn>
-void with_read(const lbm_lattice* L, Fn&& fn) {
+void with_read(const lbm_lattice* L, bool hint, Fn&& fn) {
   ReadArgs r;
   r.rows = L->rows_all;
   r.t = (long long)L->t;
@@ -174,7 +178,7 @@ void with_read(const lbm_lattice* L, Fn&& fn) {
   r.general = L->split_odd ? bc.nonper & ~(bc.wall & 15u) : ALL_GENERAL;
   auto go = [&](auto q_c, auto odd_c, auto bc_c) {
     if constexpr (!decltype(odd_c)::value) {
-      if (!L->resident) {
+      if (hint) {
         fn(q_c, odd_c, bc_c, std::true_type{}, r);
         return;
       }
@@ -254,7 +258,7 @@ void Ops<S>::set_populations(const lbm_lattice* L, const void* f, bool f64) {
 
 template <typename S>
 void Ops<S>::get_populations(const lbm_lattice* L, void* f, bool f64) {
-  with_read(L, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
+  with_read(L, !L->resident, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
     constexpr int Q = decltype(q_c)::value;
     constexpr bool BC = decltype(bc_c)::value, NT = decltype(nt_c)::value;
     with_field(f64, [&](auto v) {
@@ -285,7 +289,7 @@ void Ops<S>::get_populations(const lbm_lattice* L, void* f, bool f64) {
 
 template <typename S>
 void Ops<S>::macroscopic(const lbm_lattice* L, void* rho, void* u, bool f64, int rho_mode) {
-  with_read(L, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
+  with_read(L, L->nt_read, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
     with_field(f64, [&](auto v) {
       using O = decltype(v);
       hipLaunchKernelGGL((macroscopic_kernel<decltype(q_c)::value, S, decltype(odd_c)::value,
@@ -298,7 +302,7 @@ void Ops<S>::macroscopic(const lbm_lattice* L, void* rho, void* u, bool f64, int
 
 template <typename S>
 void Ops<S>::stats_accumulate(const lbm_lattice* L, double* sums) {
-  with_read(L, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
+  with_read(L, !L->resident, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
     hipLaunchKernelGGL((stats_accumulate_kernel<decltype(q_c)::value, S, decltype(odd_c)::value,
                                                 decltype(bc_c)::value, decltype(nt_c)::value>),
                        dim3(L->tiles_all), dim3(256), 0, L->stream, L->args, r, sums);
@@ -307,7 +311,7 @@ void Ops<S>::stats_accumulate(const lbm_lattice* L, double* sums) {
 
 template <typename S>
 void Ops<S>::reduce_partial(const lbm_lattice* L, unsigned blocks, double* partial) {
-  with_read(L, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
+  with_read(L, L->nt_read, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
     hipLaunchKernelGGL((reduce_partial_kernel<decltype(q_c)::value, S, decltype(odd_c)::value,
                                               decltype(bc_c)::value, decltype(nt_c)::value>),
                        dim3(blocks), dim3(256), 0, L->stream, L->args, r, partial);
