@@ -1104,8 +1104,8 @@ __global__ __launch_bounds__(256) void link_kernel(const LatArgs a, const int32_
 // 131x97x111 within the last-level cache). FP16: nine slabs, one node
 // (954 us, against 1567 for one slab and eight nodes). SOLID: three slabs and
 // two nodes, as the mask is read once per group (152 us; 183 us by single
-// slabs, 173 us for all at once).
-template <typename S, bool SOLID, typename O, int G, int U, bool NT>
+// slabs, 173 us for all at once). ONT: streaming hint on the stores.
+template <typename S, bool SOLID, typename O, int G, int U, bool NT, bool ONT = true>
 __global__ __launch_bounds__(256) void get_slabs_kernel(const LatArgs a, O* out) {
   const size_t N = (size_t)a.N, q0 = (size_t)blockIdx.y * G;
   const S* __restrict__ F = (const S*)a.f + q0 * N;
@@ -1127,13 +1127,13 @@ __global__ __launch_bounds__(256) void get_slabs_kernel(const LatArgs a, O* out)
       bool solid = false;
       if constexpr (SOLID) solid = a.solid_nb[i] >> 31;
 #pragma unroll
-      for (int g = 0; g < G; ++g) st<true>(out + g * N + i, solid ? O(0) : O((double)v[k][g]));
+      for (int g = 0; g < G; ++g) st<ONT>(out + g * N + i, solid ? O(0) : O((double)v[k][g]));
     }
   }
 }
 
 // Odd parity: a node per lane.
-template <int Q, typename S, bool BC, typename O>
+template <int Q, typename S, bool BC, typename O, bool ONT>
 __global__ __launch_bounds__(256) void get_populations_kernel(const LatArgs a, const ReadArgs r,
                                                               O* out) {
   const uint32_t i = xcd_tile(r.rows.by_xcd) * 256u + threadIdx.x;
@@ -1141,7 +1141,7 @@ __global__ __launch_bounds__(256) void get_populations_kernel(const LatArgs a, c
   double f[Q];
   read_node<Q, S, true, BC, false>(a, r, i, f);
 #pragma unroll
-  for (int k = 0; k < Q; ++k) st<true>(out + (size_t)k * a.N + i, O(f[k]));
+  for (int k = 0; k < Q; ++k) st<ONT>(out + (size_t)k * a.N + i, O(f[k]));
 }
 
 template <int Q, typename S, typename O>

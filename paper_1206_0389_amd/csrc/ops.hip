@@ -256,34 +256,53 @@ void Ops<S>::set_populations(const lbm_lattice* L, const void* f, bool f64) {
   });
 }
 
+// The stores carry the streaming hint, except where lattice and output fit the
+// last-level cache together and the output's slabs are not whole memory lines
+// (a line that two waves write is then written once). Stores with / without
+// it, us at even and odd parity: 111x93x121 FCLB FP16 (193 MiB) 49.5 / 34.8
+// and 48.3 / 31.0, MRT FP32 (181 MiB) 30.5 / 28.8 and 32.6 / 28.9; whole lines,
+// 64^3 FCLB FP32 7.3 / 10.4 and 9.2 / 9.2; 300 MiB, 90^3 FCLB FP64 45.9 / 53.5.
 template <typename S>
 void Ops<S>::get_populations(const lbm_lattice* L, void* f, bool f64) {
+  const size_t osize = f64 ? 8 : 4;
+  const bool keep = (L->N * osize) % 128 != 0 &&
+                    (double)L->N * L->Q * (double)(sizeof(S) + osize) <= 256.0 * 1048576.0;
   with_read(L, !L->resident, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
     constexpr int Q = decltype(q_c)::value;
     constexpr bool BC = decltype(bc_c)::value, NT = decltype(nt_c)::value;
-    with_field(f64, [&](auto v) {
-      using O = decltype(v);
-      if constexpr (decltype(odd_c)::value) {
-        hipLaunchKernelGGL((get_populations_kernel<Q, S, BC, O>), dim3(L->tiles_all), dim3(256),
-                           0, L->stream, L->args, r, (O*)f);
-      } else {
-        auto go = [&](auto solid_c) {
-          constexpr bool HALF = std::is_same_v<S, _Float16>, SOLID = decltype(solid_c)::value;
-          constexpr int G = HALF || (SOLID && Q == 19) ? (Q == 27 ? 9 : 19) : (SOLID ? 3 : 1);
-          constexpr int U = HALF || G > 3 ? 1 : (SOLID ? 2 : (NT ? 8 : 4));
-          const dim3 grid((unsigned)((L->N + 256 * U - 1) / (256 * U)), Q / G);
-          hipLaunchKernelGGL((get_slabs_kernel<S, SOLID, O, G, U, NT>), grid, dim3(256), 0,
-                             L->stream, L->args, (O*)f);
-        };
-        if constexpr (BC) {
-          if (L->solids) {
-            go(std::true_type{});
-            return;
+    auto by_field = [&](auto ont_c) {
+      constexpr bool ONT = decltype(ont_c)::value;
+      with_field(f64, [&](auto v) {
+        using O = decltype(v);
+        if constexpr (decltype(odd_c)::value) {
+          hipLaunchKernelGGL((get_populations_kernel<Q, S, BC, O, ONT>), dim3(L->tiles_all),
+                             dim3(256), 0, L->stream, L->args, r, (O*)f);
+        } else {
+          auto go = [&](auto solid_c) {
+            constexpr bool HALF = std::is_same_v<S, _Float16>, SOLID = decltype(solid_c)::value;
+            constexpr int G = HALF || (SOLID && Q == 19) ? (Q == 27 ? 9 : 19) : (SOLID ? 3 : 1);
+            constexpr int U = HALF || G > 3 ? 1 : (SOLID ? 2 : (NT ? 8 : 4));
+            const dim3 grid((unsigned)((L->N + 256 * U - 1) / (256 * U)), Q / G);
+            hipLaunchKernelGGL((get_slabs_kernel<S, SOLID, O, G, U, NT, ONT>), grid, dim3(256), 0,
+                               L->stream, L->args, (O*)f);
+          };
+          if constexpr (BC) {
+            if (L->solids) {
+              go(std::true_type{});
+              return;
+            }
           }
+          go(std::false_type{});
         }
-        go(std::false_type{});
+      });
+    };
+    if constexpr (!NT) {  // what fits together is not read with the hint
+      if (keep) {
+        by_field(std::false_type{});
+        return;
       }
-    });
+    }
+    by_field(std::true_type{});
   });
 }
 
