@@ -44,7 +44,7 @@ struct lbm_lattice {
   // last-level cache, where populations (even steps, which run over them from
   // end to end) or rows (odd steps) are whole memory lines.
   bool nt_even = false, nt_odd = false;
-  bool nt_read = false;  // of density, velocity and sums at even parity (see with_read)
+  bool nt_read = false;  // of the readouts but populations (see with_read)
   // health check inside lbm_step (lbm_set_check)
   int64_t check_every = 0;
   double check_tol = -1.0, check_m0 = 0.0;

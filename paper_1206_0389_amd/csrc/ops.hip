@@ -162,11 +162,12 @@ void with_field(bool f64, Fn&& fn) {
 
 // Runs fn(Q, odd parity, boundaries, streaming hint, ReadArgs) for a readout.
 // The hint at even parity, whose accesses run from end to end, on lattices
-// larger than the last-level cache: by `hint`, over a third larger for what
-// reads the populations and little else. Up to there enough of them is still
-// cached (density and velocity after two steps with / without it, us: 270 MiB
-// MRT FP32 161x153x151 67.5 / 57.9, 304 MiB MRT FP64 128^3 68 / 55; 383 MiB
-// FCLB FP32 161x153x151 71 / 118). Workgroups per CU are not limited here: fewer
+// larger than the last-level cache: by `hint`, over a third larger except for
+// the populations themselves. Up to there enough of them is still cached
+// (density and velocity after two steps with / without it, us: 270 MiB MRT
+// FP32 161x153x151 67.5 / 57.9, 304 MiB MRT FP64 128^3 68 / 55; 383 MiB FCLB
+// FP32 161x153x151 71 / 118; statistics 129 / 115, 97 / 77; 134 / 192; the
+// populations' copy 108 / 108, 96 / 101; 122 / 140). Workgroups per CU are not limited here: fewer
 // cost (256x256x512 FCLB FP16, density and velocity: 382 us; 455 us with
 // three).
 template <typename Fn>
@@ -321,7 +322,7 @@ void Ops<S>::macroscopic(const lbm_lattice* L, void* rho, void* u, bool f64, int
 
 template <typename S>
 void Ops<S>::stats_accumulate(const lbm_lattice* L, double* sums) {
-  with_read(L, !L->resident, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
+  with_read(L, L->nt_read, [&](auto q_c, auto odd_c, auto bc_c, auto nt_c, const ReadArgs& r) {
     hipLaunchKernelGGL((stats_accumulate_kernel<decltype(q_c)::value, S, decltype(odd_c)::value,
                                                 decltype(bc_c)::value, decltype(nt_c)::value>),
                        dim3(L->tiles_all), dim3(256), 0, L->stream, L->args, r, sums);
