@@ -794,10 +794,10 @@ __device__ __forceinline__ void step_node(const LatArgs& a, const Node& n, long 
 }
 
 // Waves per SIMD that the general rules have to leave to the wall rows of the
-// same launch: FP32 and FP16 steps need three and four (see lds_limit).
+// same launch: three in FP32, two in FP64 (see lds_limit).
 template <typename S, int ROWS>
 constexpr int step_waves() {
-  return ROWS != ROWS_SPLIT ? 1 : (sizeof(S) == 8 ? 2 : (sizeof(S) == 4 ? 3 : 4));
+  return ROWS != ROWS_SPLIT ? 1 : (sizeof(S) == 8 ? 2 : 3);
 }
 
 // SPLIT: an odd step with boundaries in one launch. The rows on faces other
@@ -827,15 +827,16 @@ __global__ __launch_bounds__(256, (step_waves<S, ROWS>())) void step_kernel(
   } else {
     int x, y, z;
     if constexpr (ROWS == ROWS_SPLIT) {
+      static_assert(ODD && !EXT && sizeof(S) > 2, "launched without solids, free slip, pressure");
       if (blockIdx.x < r.list_tiles) {
         if (!list_coords(a, r, x, y, z)) return;
         n = make_node(a, x, y, z);
-        step_node<KIND, S, ODD, BC_GENERAL, EXT, false>(a, n, t, rec);
+        step_node<KIND, S, true, BC_GENERAL, false, false>(a, n, t, rec);
         return;
       }
       if (!flat_coords(a, r, r.list_tiles, x, y, z)) return;
       n = make_node(a, x, y, z);
-      step_node<KIND, S, ODD, BC_WALLS, false, NT>(a, n, t, rec);
+      step_node<KIND, S, true, BC_WALLS, false, NT>(a, n, t, rec);
       return;
     }
     if (!(ROWS == ROWS_LIST ? list_coords(a, r, x, y, z) : flat_coords(a, r, 0, x, y, z))) return;
