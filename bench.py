@@ -653,7 +653,7 @@ def main():
     roof = {"bound": "hbm", "achieved": main_res["achieved_GBs"], "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": main_res["achieved_GBs"] / HBM_PEAK_GBS,
             "traffic": None,
-            "traffic_unit": "bytes per step (one even launch, or the two odd launches)",
+            "traffic_unit": "bytes per step (mean of an even and an odd step)",
             "kernel": ("refined coarse step (level steps and interface kernels) <%s,%s>"
                        if refined else "step_kernel<%s,%s>") % (model, storage),
             "algorithmic_bytes_per_launch": alg_per_launch,

@@ -293,11 +293,10 @@ int lbm_set_check(lbm_lattice* lat, int64_t every, double mass_tol);
  * (FP64), stream-ordered on the lattice's stream, no host copy and no
  * synchronisation; the caller checks finiteness. The partial sums live in a
  * library-owned static device array (16384 rows of five doubles, about
- * 640 KiB per device, held until the process ends): z planes fold into the
- * blocks of one x-y plane, so the summation order differs from lbm_reduce's
- * (equal up to FP64 rounding). Nothing is allocated. Returns LBM_EINVAL if
- * an x-y plane needs more than 16384 blocks of 256 nodes
- * (ceil(nx / bx) * ceil(ny / by), bx = min(nx, 256), by = 256 / bx).
+ * 640 KiB per device, held until the process ends); blocks and order of the
+ * sums are lbm_reduce's. Nothing is allocated. Lattices whose x-y plane has
+ * more than 16384 blocks of 256 nodes (ceil(nx / bx) * ceil(ny / by), bx =
+ * min(nx, 256), by = 256 / bx) are refused with LBM_EINVAL.
  * Every call on one device shares the array: calls that overlap on one
  * device (different streams, threads or lattices) race. */
 int lbm_reduce_static(lbm_lattice* lat, double* out);

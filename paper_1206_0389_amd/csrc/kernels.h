@@ -108,9 +108,10 @@ struct FastDiv {
 // rows of every other z. SPLIT: both, LIST in the first list_tiles workgroups
 // (general rules), FLAT in the others (wall rows).
 //
-// FLAT against BOX for the steps (131 x 97 x 211 MRT FP32, even / odd with
-// walls): 68.9 / 72.5 us against 78.7 / 81.0, as no lane idles at row ends and
-// waves are 256 B runs; 256-node rows: the same. by_xcd: see xcd_tile.
+// FLAT: no lane idles at row ends and every wave is one contiguous run. 131 x
+// 97 x 211 MRT FP32 jet, even / odd step: 141 / 106 us with workgroups of whole
+// rows and the streaming hint at every size, 62 / 63 so; 256-node rows take the
+// same time either way. by_xcd: see xcd_tile.
 struct Rows {
   int y0, ny_in;
   int zb_n, zb[2];
@@ -848,8 +849,9 @@ __global__ __launch_bounds__(256, (step_waves<S, ROWS>())) void step_kernel(
 // Even step of FP16 storage with two neighbouring nodes per lane (an even
 // number of nodes): one 4-byte load and store per population serve both,
 // where one node per lane moves 2 bytes per access. Each node collides in
-// FP32 exactly as in step_kernel (bitwise the same result). No solids, links,
-// pressure faces or recording (those lattices take step_kernel).
+// FP32 exactly as in step_kernel (bitwise the same result). Not for PRESSURE
+// faces and recording, which take step_kernel. Solid nodes run it too (nothing
+// reads their populations), and links follow in their own launch.
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 template <int KIND, bool BC, bool NT>
 __global__ __launch_bounds__(256) void step_even_pair_kernel(const LatArgs a, bool by_xcd) {

@@ -141,10 +141,13 @@ void default_bc(BcArgs& b) {
   b.ghost_n = 1;
 }
 
-// Blocks of a reduction: as many as run at once, each summing several tiles,
-// so that the single block that adds up their rows has little to do.
+// Blocks of a reduction: four per CU, each summing several tiles, so that the
+// single block that adds up their rows has little to do. All of them run at
+// once, except at odd parity with boundaries, where the general pull's
+// registers leave room for two (D3Q27) or three (D3Q19) per CU.
+constexpr unsigned kReduceBlocks = 1024;
 unsigned reduce_blocks(const lbm_lattice* L) {
-  return L->tiles_all < 1024u ? L->tiles_all : 1024u;
+  return L->tiles_all < kReduceBlocks ? L->tiles_all : kReduceBlocks;
 }
 
 // FP64 sums of the current state (lbm_reduce's definition), blocking.
@@ -183,11 +186,12 @@ int run_check(lbm_lattice* L) {
 }  // namespace
 
 // Library-owned partial sums for lbm_reduce_static: one row of five per block
-// of an x-y plane of the reduce launch, then the five results. Each device
-// holds its own copy for the life of the process; every call on a device
-// shares it.
+// of the reduce launch (kReduceBlocks at most). Each device holds its own copy
+// for the life of the process; every call on a device shares it. The number of
+// rows is the limit that the call documents for an x-y plane.
 constexpr size_t kStaticPartials = 16384;
 static __device__ __align__(256) double scratch[kStaticPartials * 5 + 8];
+static_assert(kReduceBlocks <= kStaticPartials);
 
 namespace {
 

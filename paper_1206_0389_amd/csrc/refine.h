@@ -396,7 +396,12 @@ __device__ __forceinline__ void level_node(const Lev& L, const int (&g)[3], int 
 // One launch for the three classes: the general tiles are few and take a long
 // chain of loads and rules each, alone 58 us on level 0 and 17 us on level 1
 // of a 96x96x192 jet with 128x128x192 fine nodes (FCLB FP32), before the
-// others could start.
+// others could start. It costs the plain tiles waves (FCLB four per SIMD in
+// place of eight in FP32, three of seven in FP64) and is the faster everywhere
+// all the same: four steps of the jet with half its cross-section at level 1,
+// us in three launches / one, 32^2 x 64 and 128^2 x 256 cells of level 0: FCLB
+// FP32 558 / 503, 5630 / 5262, FP16 505 / 452, 4056 / 3791, MRT FP32 470 / 420,
+// 3780 / 3686; 112^2 x 224 FCLB FP64 6677 / 6093, MRT FP64 4393 / 4299.
 template <int KIND, typename S>
 __global__ __launch_bounds__(256) void level_step_kernel(const Lev L, const int* tiles,
                                                          unsigned ngeneral, unsigned nwalls,
