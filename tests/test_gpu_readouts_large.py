@@ -1,10 +1,11 @@
-"""Density, velocity and sums read with the streaming hint, which they take on
+"""Density, velocity, sums and statistics read with the streaming hint, which they take on
 lattices more than a third larger than the last-level cache: node counts that
 leave the last workgroup, lane and memory line partly used, at even parity.
 
 Populations come back as they are stored; the other readouts are functions of
 them and differ by the rounding of their sums only, 64 units of FP64 (27 terms,
-twice, and a division), sums over N nodes by N units of the sum of magnitudes."""
+twice, and a division), sums over N nodes by N units of the sum of magnitudes;
+squares of velocities by four times the velocities' units."""
 import pytest
 
 from lbm_cases import gpu_lattice
@@ -40,3 +41,8 @@ def test_readouts_with_the_hint(name, storage, shape):
     for k, ref in enumerate([d, j[0], j[1], j[2]]):
         bar = (64 + ref.numel()) * U64 * float(ref.abs().sum() + top * 64)
         assert abs(s[k] - float(ref.sum())) <= bar, k
+    sums = g.stats_buffer()
+    g.stats_accumulate(sums)
+    got = sums.reshape(6, nz, ny, nx)
+    assert float((got[:3] - u).abs().max()) <= 128 * U64 * top
+    assert float((got[3:] - u * u).abs().max()) <= 512 * U64 * max(top, top * top)
